@@ -250,8 +250,9 @@ typedef struct sv_stats {
   int64_t by_variant[6];    /* gate applications per SV_VARIANT_* */
   int64_t permute_sweeps;   /* full-sweep tile permutation passes */
   int64_t layout_only;      /* fused gates that only permute their qubits: applied to the layout map, no sweep */
-  int64_t diag_chunks;      /* 16-byte chunks the diagonal blocks' sweeps read and wrote (a full sweep is
-                               2^(N-1); entries exactly 1 need no visit, so a block may sweep less) */
+  int64_t diag_chunks;      /* 16-byte chunks the diagonal blocks' sweeps read and write on their own (a full
+                               sweep is 2^(N-1); entries exactly 1 need no visit, so a block may sweep less);
+                               blocks that ride in a pass of sv_run_plan count the same */
 } sv_stats;
 int sv_get_stats(const sv_state *s, sv_stats *out);
 

@@ -159,9 +159,14 @@ int sv_plan_swaps(sv_plan *p, const float *mlp_params_host, int mlp_nin, int mlp
  * *is_swap = 0. */
 int sv_plan_block_swap(const sv_plan *p, int i, int *is_swap, int32_t *dest);
 
-/* Apply every block in order: fused blocks through sv_apply_fused, layout-
- * swap blocks through sv_permute_layout (each listed logical qubit moved to
- * its physical bit, the qubit found there taking its old place). */
+/* Apply every block: the state afterwards is that of sv_apply_fused block by
+ * block (layout-swap blocks through sv_permute_layout: each listed logical
+ * qubit moved to its physical bit, the qubit found there taking its old
+ * place).  With the selector options at their defaults, blocks that fit run
+ * several to a pass over the state (FP32: dense blocks of up to 6 qubits and
+ * diagonal ones; BF16x3: diagonal blocks of entries 1, -1, i, -i), blocks on
+ * different qubits in either order; statistics count blocks as before, and
+ * launches the kernels that ran. */
 int sv_run_plan(sv_state *s, const sv_plan *p);
 
 int sv_plan_free(sv_plan *p);
@@ -180,7 +185,8 @@ int sv_plan_free(sv_plan *p);
  *   sv_plan_bind        lower every block, copy the operands into op_dev
  *                       (caller-owned device memory, >= sv_bound_bytes,
  *                       256-B aligned; the copy completes before return)
- *   sv_bound_run        launch every block in order (asynchronous)
+ *   sv_bound_run        launch every block (asynchronous), cut into the passes
+ *                       sv_run_plan would run
  *   sv_bound_graph_run  first call: capture the launches into a HIP graph on
  *                       the handle's stream and instantiate it; every call:
  *                       launch the graph (asynchronous).  The graph holds

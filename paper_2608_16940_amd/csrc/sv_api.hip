@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <cmath>
 #include <climits>
+#include <memory>
 #include <utility>
 #include <cstdio>
 #include <cstring>
@@ -13,7 +14,9 @@
 #include "sv_diagcover.h"
 #include "sv_permute_host.h"
 #include "sv_internal.h"
+#include "sv_pass.h"
 #include "sv_plan.h"
+#include "sv_plan_types.h"
 
 namespace sv {
 
@@ -388,6 +391,178 @@ int apply_physical(sv_state *s, const double *matrix, const int32_t *A, int k) {
   if (rc) return rc;
   for (auto &pr : L.relabel) swap_physical(s, pr.first, pr.second);
   s->stats.relabels += int64_t(L.relabel.size());
+  return SV_OK;
+}
+
+// ------------------------------------------------------------------ gate sequences
+// A sequence known in full (a plan, a bound plan) is cut into steps: fused
+// tile passes (sv_pass_host.h) and single sweeps.  Handles with a forced
+// lowering or any non-default selector option run every gate by itself.
+bool fusible(const sv_state *s) {
+  return s->variant == SV_VARIANT_AUTO && s->dm_n == 0 && !s->lazy && s->mfma_min_k == 4 && s->opsrc == SV_MFMA_OPERAND_AUTO &&
+         s->tile_order == -1;
+}
+
+void add_stats(sv_stats *a, const sv_stats &d) {
+  a->gate_sweeps += d.gate_sweeps;
+  a->launches += d.launches;
+  a->layout_only += d.layout_only;
+  for (int v = 0; v < 6; ++v) a->by_variant[v] += d.by_variant[v];
+  a->diag_chunks += d.diag_chunks;
+}
+
+struct SeqGate {
+  const double *m;
+  const int32_t *t;  // logical targets
+  int k;
+};
+
+struct Sequence {
+  std::vector<pass::Item> items;  // the gates that touch the state, on physical bits
+  std::vector<pass::Step> steps;
+  int32_t Lend[64];               // the layout a run leaves
+  sv_stats add;                   // the statistics a run adds, launches of single sweeps apart
+};
+
+bool valid_targets(int n, const int32_t *t, int k) {
+  if (k < 1 || k > n || k > SV_MAX_K) return false;
+  for (int j = 0; j < k; ++j) {
+    if (t[j] < 0 || t[j] >= n) return false;
+    for (int i = 0; i < j; ++i)
+      if (t[i] == t[j]) return false;
+  }
+  return true;
+}
+
+bool is_diagonal(const double *m, int k) {
+  const int D = 1 << k;
+  for (int r = 0; r < D; ++r)
+    for (int c = 0; c < D; ++c)
+      if (r != c && (m[2 * (r * D + c)] != 0.0 || m[2 * (r * D + c) + 1] != 0.0)) return false;
+  return true;
+}
+
+// Resolves the gates from layout L on and cuts them into steps; every gate valid.
+void plan_sequence(const sv_state *s, const std::vector<SeqGate> &gates, const int32_t *L0, Sequence *q) {
+  const int n = s->n;
+  std::memset(&q->add, 0, sizeof(q->add));
+  std::memcpy(q->Lend, L0, sizeof(q->Lend));
+  int32_t *L = q->Lend;
+  for (const SeqGate &g : gates) {
+    int perm[SV_MAX_K];
+    if (qubit_permutation(g.m, g.k, perm)) {  // as sv_apply_fused
+      int32_t old[SV_MAX_K];
+      for (int j = 0; j < g.k; ++j) old[j] = L[g.t[j]];
+      for (int j = 0; j < g.k; ++j) L[g.t[perm[j]]] = old[j];
+      q->add.layout_only += 1;
+      continue;
+    }
+    pass::Item it;
+    it.k = g.k;
+    it.m = g.m;
+    for (int j = 0; j < g.k; ++j) it.A[j] = L[g.t[j]];
+    it.diag = is_diagonal(g.m, g.k);
+    q->add.gate_sweeps += 1;
+    int v = SV_VARIANT_GENERIC;  // the lowering the gate has on its own
+    if (it.diag) {
+      v = SV_VARIANT_DIAG;
+      const int D = 1 << g.k;
+      it.exact = true;
+      double dd[512];
+      for (int r = 0; r < D; ++r) {
+        dd[2 * r] = g.m[2 * (size_t(r) * D + r)];
+        dd[2 * r + 1] = g.m[2 * (size_t(r) * D + r) + 1];
+        const double re = std::fabs(dd[2 * r]), im = std::fabs(dd[2 * r + 1]);
+        it.exact = it.exact && ((re == 1.0 && im == 0.0) || (re == 0.0 && im == 1.0));
+      }
+      const DiagCover cv = diag_cover(g.k, dd, it.A);
+      it.sweep = double(cv.nsub) * kDiagLaunchCost;
+      for (int i = 0; i < cv.nsub; ++i) {
+        const int f = __builtin_popcount(cv.mask[i]);
+        it.sweep += std::ldexp(1.0, -f);
+        q->add.diag_chunks += (int64_t(1) << (n - 1)) >> f;
+      }
+      q->add.by_variant[v] += 1;
+      if (cv.nsub == 0) continue;  // the identity
+    } else {
+      if (g.k == 1 && it.A[0] <= 6)
+        v = SV_VARIANT_SHUFFLE;
+      else if (g.k >= 4 && g.k <= 7 && n >= g.k + mfma_tile_M(g.k))
+        v = SV_VARIANT_MFMA;
+      else if (g.k <= 4)
+        v = SV_VARIANT_VALU;
+      q->add.by_variant[v] += 1;
+    }
+    q->items.push_back(it);
+  }
+  q->steps = pass::build_steps(n, q->items, s->prec);
+}
+
+void finish_sequence(sv_state *s, const Sequence &q, const std::vector<SeqGate> &gates) {
+  for (int i = 0; i < s->n; ++i) {
+    s->L[i] = q.Lend[i];
+    s->Linv[q.Lend[i]] = i;
+  }
+  for (const SeqGate &g : gates) {
+    ++s->clock;
+    for (int j = 0; j < g.k; ++j) s->last_use[g.t[j]] = s->clock;
+  }
+}
+
+int launch_pass(sv_state *s, const pass::Fused &f, const char *dev) {
+  const hipError_t e = pass::launch(s->n, f, s->amps, dev, s->st);
+  if (e != hipSuccess) {
+    set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
+    return SV_ERR_DEVICE;
+  }
+  return SV_OK;
+}
+
+// Runs valid gates in order through fused passes.
+int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
+  Sequence q;
+  plan_sequence(s, gates, s->L, &q);
+  const sv_stats before = s->stats;
+  int64_t launches = 0;
+  for (size_t i = 0; i < q.steps.size();) {
+    if (q.steps[i].pass.S == 0) {
+      const int64_t l0 = s->stats.launches;
+      const pass::Item &it = q.items[size_t(q.steps[i].items[0])];
+      const int rc = apply_physical(s, it.m, it.A, it.k);
+      if (rc) return rc;
+      launches += s->stats.launches - l0;
+      ++i;
+      continue;
+    }
+    // consecutive passes share a staging slot while they fit
+    size_t j = i, bytes = 0;
+    std::vector<size_t> off;
+    while (j < q.steps.size() && q.steps[j].pass.S > 0 &&
+           (j == i || bytes + align256(q.steps[j].pass.data.size()) <= kRingSlotBytes)) {
+      off.push_back(bytes);
+      bytes += align256(q.steps[j].pass.data.size());
+      ++j;
+    }
+    std::vector<char> host(bytes);
+    for (size_t x = i; x < j; ++x)
+      std::memcpy(host.data() + off[x - i], q.steps[x].pass.data.data(), q.steps[x].pass.data.size());
+    void *dev = nullptr;
+    int slot = 0;
+    int rc = stage(s, host.data(), bytes, &dev, &slot);
+    if (rc) return rc;
+    for (size_t x = i; x < j; ++x) {
+      rc = launch_pass(s, q.steps[x].pass, static_cast<const char *>(dev) + off[x - i]);
+      if (rc) return rc;
+      ++launches;
+    }
+    rc = release_slot(s, slot);
+    if (rc) return rc;
+    i = j;
+  }
+  s->stats = before;
+  q.add.launches = launches;
+  add_stats(&s->stats, q.add);
+  finish_sequence(s, q, gates);
   return SV_OK;
 }
 
@@ -879,10 +1054,16 @@ int sv_get_stats(const sv_state *s, sv_stats *out) {
 }  // extern "C"
 
 // ------------------------------------------------------------------ bound plans
+// One launch of a bound plan: a fused pass (pass.S > 0) or a lowered gate.
+struct BoundStep {
+  Lowered gate;
+  pass::Fused pass;
+  size_t off = SIZE_MAX;  // operand offset in op_dev (SIZE_MAX: by value)
+};
+
 struct sv_bound {
   sv_state *s = nullptr;
-  std::vector<Lowered> ops;  // variant -1: a qubit permutation, absorbed by the layout map
-  std::vector<size_t> off;   // operand offset in op_dev (SIZE_MAX: by value)
+  std::vector<BoundStep> steps;
   char *op_dev = nullptr;
   int32_t L[64];             // layout a run starts from
   int32_t Lend[64];          // layout a run leaves (after the absorbed permutations)
@@ -894,60 +1075,78 @@ struct sv_bound {
 
 namespace {
 
-int lower_plan(sv_state *s, const sv_plan *p, std::vector<Lowered> *ops, std::vector<size_t> *off, size_t *bytes,
-               int32_t *Lend) {
+int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
   if (s->lazy) {
     set_error("bound plans need lazy relabel off");
     return SV_ERR_ARG;
   }
-  int nb = 0;
-  int rc = sv_plan_num_blocks(p, &nb);
-  if (rc) return rc;
-  ops->assign(static_cast<size_t>(nb), Lowered());
-  off->assign(static_cast<size_t>(nb), SIZE_MAX);
-  size_t total = 0;
-  int32_t L[64];  // the layout as the run will see it block by block
-  std::memcpy(L, s->L, sizeof(L));
-  for (int i = 0; i < nb; ++i) {
-    int sw = 0;
-    rc = sv_plan_block_swap(p, i, &sw, nullptr);
-    if (rc) return rc;
-    if (sw) {
+  b->s = s;
+  std::memcpy(b->L, s->L, sizeof(b->L));
+  std::memcpy(b->Lend, s->L, sizeof(b->Lend));
+  std::memset(&b->per_run, 0, sizeof(b->per_run));
+  std::vector<SeqGate> gates;
+  for (const SvBlock &k : p->blocks) {
+    if (k.swap) {
       set_error("a plan with layout-swap blocks runs through sv_run_plan, not as a bound plan");
       return SV_ERR_UNSUPPORTED;
     }
-    int k = 0, ng = 0, dg = 0;
-    int32_t t[8];
-    rc = sv_plan_block_info(p, i, &k, t, &ng, &dg);
+    if (!valid_targets(s->n, k.tuple.data(), k.k)) {
+      set_error("plan target outside the state");
+      return SV_ERR_ARG;
+    }
+    gates.push_back({k.matrix.data(), k.tuple.data(), k.k});
+  }
+  size_t total = 0;
+  auto take = [&](BoundStep &st, size_t n) {
+    st.off = total;
+    total += align256(n);
+  };
+  auto add_gate = [&](const double *m, const int32_t *A, int k) -> int {
+    BoundStep st;
+    const int rc = lower(s, m, A, k, false, &st.gate);
     if (rc) return rc;
-    std::vector<double> m(size_t(2) << (2 * k));
-    rc = sv_plan_block_matrix(p, i, m.data());
-    if (rc) return rc;
-    int32_t A[8];
-    for (int j = 0; j < k; ++j) {
-      if (t[j] < 0 || t[j] >= s->n) {
-        set_error("plan target outside the state");
-        return SV_ERR_ARG;
+    if (!st.gate.op.empty()) take(st, st.gate.op.size());
+    b->per_run.launches += st.gate.variant == SV_VARIANT_DIAG ? st.gate.cover.nsub : 1;
+    b->steps.push_back(std::move(st));
+    return SV_OK;
+  };
+  if (fusible(s)) {
+    Sequence q;
+    plan_sequence(s, gates, s->L, &q);
+    b->per_run = q.add;
+    for (pass::Step &x : q.steps) {
+      if (x.pass.S == 0) {
+        const pass::Item &it = q.items[size_t(x.items[0])];
+        const int rc = add_gate(it.m, it.A, it.k);
+        if (rc) return rc;
+        continue;
       }
-      A[j] = L[t[j]];
+      BoundStep st;
+      st.pass = std::move(x.pass);
+      take(st, st.pass.data.size());
+      b->per_run.launches += 1;
+      b->steps.push_back(std::move(st));
     }
-    int perm[SV_MAX_K];
-    if (s->variant == SV_VARIANT_AUTO && qubit_permutation(m.data(), k, perm)) {  // as sv_apply_fused
-      int32_t old[SV_MAX_K];
-      for (int j = 0; j < k; ++j) old[j] = L[t[j]];
-      for (int j = 0; j < k; ++j) L[t[perm[j]]] = old[j];
-      (*ops)[size_t(i)].variant = -1;
-      continue;
-    }
-    rc = lower(s, m.data(), A, k, false, &(*ops)[size_t(i)]);
-    if (rc) return rc;
-    if (!(*ops)[size_t(i)].op.empty()) {
-      (*off)[size_t(i)] = total;
-      total += align256((*ops)[size_t(i)].op.size());
+    std::memcpy(b->Lend, q.Lend, sizeof(b->Lend));
+  } else {
+    for (const SeqGate &g : gates) {
+      int32_t A[SV_MAX_K];
+      for (int j = 0; j < g.k; ++j) A[j] = b->Lend[g.t[j]];
+      int perm[SV_MAX_K];
+      if (s->variant == SV_VARIANT_AUTO && qubit_permutation(g.m, g.k, perm)) {  // as sv_apply_fused
+        for (int j = 0; j < g.k; ++j) b->Lend[g.t[perm[j]]] = A[j];
+        b->per_run.layout_only += 1;
+        continue;
+      }
+      const int rc = add_gate(g.m, A, g.k);
+      if (rc) return rc;
+      const Lowered &L = b->steps.back().gate;
+      b->per_run.gate_sweeps += 1;
+      if (L.variant < 6) b->per_run.by_variant[L.variant] += 1;
+      if (L.variant == SV_VARIANT_DIAG) b->per_run.diag_chunks += diag_chunks(L, s->n);
     }
   }
   *bytes = total;
-  if (Lend) std::memcpy(Lend, L, sizeof(L));
   return SV_OK;
 }
 
@@ -964,21 +1163,12 @@ int bound_check(const sv_bound *b) {
 }
 
 int bound_launch_all(sv_bound *b) {
-  for (size_t i = 0; i < b->ops.size(); ++i) {
-    if (b->ops[i].variant < 0) continue;
-    const void *dev = b->off[i] == SIZE_MAX ? nullptr : b->op_dev + b->off[i];
-    const int rc = launch_lowered(b->s, b->ops[i], dev);
+  for (const BoundStep &st : b->steps) {
+    const char *dev = st.off == SIZE_MAX ? nullptr : b->op_dev + st.off;
+    const int rc = st.pass.S > 0 ? launch_pass(b->s, st.pass, dev) : launch_lowered(b->s, st.gate, dev);
     if (rc) return rc;
   }
   return SV_OK;
-}
-
-void add_stats(sv_stats *a, const sv_stats &d) {
-  a->gate_sweeps += d.gate_sweeps;
-  a->launches += d.launches;
-  a->layout_only += d.layout_only;
-  for (int v = 0; v < 6; ++v) a->by_variant[v] += d.by_variant[v];
-  a->diag_chunks += d.diag_chunks;
 }
 
 // After a run: the handle's layout is the one the absorbed permutations leave.
@@ -994,15 +1184,85 @@ void bound_finish(sv_bound *b) {
 
 extern "C" {
 
+int sv_run_plan(sv_state *s, const sv_plan *p) {
+  return guard([&]() -> int {
+    if (!s || !p) {
+      set_error("null pointer");
+      return SV_ERR_ARG;
+    }
+    // next use of every logical qubit after each block: the relabel policy's
+    // view of the future (Corollary 1)
+    const size_t nb = p->blocks.size(), nq = size_t(std::max(p->n, s->n));
+    std::vector<int64_t> next(nq, INT64_MAX);
+    std::vector<std::vector<int64_t>> hints(nb);
+    const bool fuse = fusible(s);
+    for (size_t i = nb; i-- > 0;) {
+      // a fused run leaves the hints of its last block
+      if (!fuse || i + 1 == nb || p->blocks[i + 1].swap) hints[i] = next;
+      if (!p->blocks[i].swap)
+        for (int32_t q : p->blocks[i].tuple) next[size_t(q)] = int64_t(i);
+    }
+    for (size_t i = 0; i < nb;) {
+      const SvBlock &b = p->blocks[i];
+      int rc;
+      if (b.swap) {
+        // each listed qubit to its physical bit, the occupant to its old place
+        std::vector<int32_t> L(nq), Linv(nq);
+        rc = sv_get_layout(s, L.data());
+        if (rc) return rc;
+        for (int q = 0; q < p->n; ++q) Linv[size_t(L[size_t(q)])] = q;
+        for (int j = 0; j < b.k; ++j) {
+          const int32_t q = b.tuple[size_t(j)], to = b.dest[size_t(j)], from = L[size_t(q)];
+          if (from == to) continue;
+          const int32_t r = Linv[size_t(to)];
+          L[size_t(q)] = to;
+          L[size_t(r)] = from;
+          Linv[size_t(to)] = q;
+          Linv[size_t(from)] = r;
+        }
+        rc = sv_permute_layout(s, L.data());
+        if (rc) return rc;
+        ++i;
+        continue;
+      }
+      size_t j = i;
+      std::vector<SeqGate> gates;
+      if (fuse)
+        for (; j < nb && !p->blocks[j].swap; ++j) {
+          const SvBlock &k = p->blocks[j];
+          if (!valid_targets(s->n, k.tuple.data(), k.k)) break;
+          gates.push_back({k.matrix.data(), k.tuple.data(), k.k});
+        }
+      if (j > i) {
+        if (!hints[j - 1].empty()) {
+          rc = sv_hint_next_use(s, hints[j - 1].data());
+          if (rc) return rc;
+        }
+        rc = run_gates(s, gates);
+        if (rc) return rc;
+        i = j;
+        continue;
+      }
+      if (!hints[i].empty()) {
+        rc = sv_hint_next_use(s, hints[i].data());
+        if (rc) return rc;
+      }
+      rc = sv_apply_fused(s, b.matrix.data(), b.tuple.data(), b.k);
+      if (rc) return rc;
+      ++i;
+    }
+    return SV_OK;
+  });
+}
+
 int sv_bound_bytes(sv_state *s, const sv_plan *p, size_t *out) {
   return guard([&]() -> int {
     if (!s || !p || !out) {
       set_error("null pointer");
       return SV_ERR_ARG;
     }
-    std::vector<Lowered> ops;
-    std::vector<size_t> off;
-    return lower_plan(s, p, &ops, &off, out, nullptr);
+    sv_bound b;
+    return lower_plan(s, p, &b, out);
   });
 }
 
@@ -1012,49 +1272,32 @@ int sv_plan_bind(sv_state *s, const sv_plan *p, void *op_dev, size_t op_bytes, s
       set_error("null pointer");
       return SV_ERR_ARG;
     }
-    sv_bound *b = new sv_bound();
-    b->s = s;
+    std::unique_ptr<sv_bound> b(new sv_bound());
     size_t need = 0;
-    int rc = lower_plan(s, p, &b->ops, &b->off, &need, b->Lend);
-    if (rc) {
-      delete b;
-      return rc;
-    }
+    const int rc = lower_plan(s, p, b.get(), &need);
+    if (rc) return rc;
     if (need > 0 && (!op_dev || op_bytes < need || (reinterpret_cast<uintptr_t>(op_dev) & 255))) {
-      delete b;
       set_error("operand buffer missing, too small or not 256-byte aligned");
       return SV_ERR_ARG;
     }
     b->op_dev = static_cast<char *>(op_dev);
     std::vector<char> host(need);
-    for (size_t i = 0; i < b->ops.size(); ++i) {
-      if (b->off[i] == SIZE_MAX) continue;
-      std::memcpy(host.data() + b->off[i], b->ops[i].op.data(), b->ops[i].op.size());
-      b->ops[i].op.clear();
-      b->ops[i].op.shrink_to_fit();
+    for (BoundStep &st : b->steps) {
+      if (st.off == SIZE_MAX) continue;
+      std::vector<char> &src = st.pass.S > 0 ? st.pass.data : st.gate.op;
+      std::memcpy(host.data() + st.off, src.data(), src.size());
+      src.clear();
+      src.shrink_to_fit();
     }
     if (need > 0) {
       hipError_t e = hipMemcpyAsync(op_dev, host.data(), need, hipMemcpyHostToDevice, s->st);
       if (e == hipSuccess) e = hipStreamSynchronize(s->st);
       if (e != hipSuccess) {
-        delete b;
         set_error(std::string("operand upload failed: ") + hipGetErrorString(e));
         return SV_ERR_DEVICE;
       }
     }
-    std::memcpy(b->L, s->L, sizeof(b->L));
-    std::memset(&b->per_run, 0, sizeof(b->per_run));
-    for (const Lowered &L : b->ops) {
-      if (L.variant < 0) {
-        b->per_run.layout_only += 1;
-        continue;
-      }
-      b->per_run.gate_sweeps += 1;
-      b->per_run.launches += (L.variant == SV_VARIANT_DIAG) ? L.cover.nsub : 1;
-      if (L.variant < 6) b->per_run.by_variant[L.variant] += 1;
-      if (L.variant == SV_VARIANT_DIAG) b->per_run.diag_chunks += diag_chunks(L, s->n);
-    }
-    *out = b;
+    *out = b.release();
     return SV_OK;
   });
 }
@@ -1063,10 +1306,11 @@ int sv_bound_run(sv_bound *b) {
   return guard([&]() -> int {
     int rc = bound_check(b);
     if (rc) return rc;
-    const int64_t before = b->s->stats.layout_only;
+    const sv_stats before = b->s->stats;
     rc = bound_launch_all(b);
     if (rc) return rc;
-    b->s->stats.layout_only = before + b->per_run.layout_only;
+    b->s->stats = before;
+    add_stats(&b->s->stats, b->per_run);
     bound_finish(b);
     return SV_OK;
   });

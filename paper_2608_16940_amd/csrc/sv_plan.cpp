@@ -13,25 +13,11 @@
 #include "sv_permute_host.h"
 #include "sv_guard.h"
 #include "sv_mlp.h"
+#include "sv_plan_types.h"
 
 namespace sv {
 bool qubit_permutation(const double *G, int k, int *perm);
 }
-
-struct SvBlock {
-  int k = 0;
-  int ngates = 0;
-  bool diag = true;
-  std::vector<int32_t> tuple;    // ordered logical targets (ascending)
-  std::vector<double> matrix;    // complex128 interleaved, 2^k x 2^k
-  bool swap = false;             // a layout-swap block: no matrix, tuple[j] goes to physical bit dest[j]
-  std::vector<int32_t> dest;
-};
-
-struct sv_plan {
-  int n = 0;
-  std::vector<SvBlock> blocks;
-};
 
 namespace {
 
@@ -316,53 +302,6 @@ int sv_plan_block_swap(const sv_plan *p, int i, int *is_swap, int32_t *dest) {
     *is_swap = b.swap ? 1 : 0;
     if (b.swap && dest)
       for (int j = 0; j < b.k; ++j) dest[j] = b.dest[size_t(j)];
-    return SV_OK;
-  });
-}
-
-int sv_run_plan(sv_state *s, const sv_plan *p) {
-  return sv::guard([&]() -> int {
-    if (!s || !p) {
-      sv::set_error("null pointer");
-      return SV_ERR_ARG;
-    }
-    // next use of every logical qubit after each block: the relabel policy's
-    // view of the future (Corollary 1)
-    const size_t nb = p->blocks.size();
-    std::vector<int64_t> next(size_t(p->n), INT64_MAX);
-    std::vector<std::vector<int64_t>> hints(nb);
-    for (size_t i = nb; i-- > 0;) {
-      hints[i] = next;
-      if (!p->blocks[i].swap)
-        for (int32_t q : p->blocks[i].tuple) next[size_t(q)] = int64_t(i);
-    }
-    for (size_t i = 0; i < nb; ++i) {
-      const SvBlock &b = p->blocks[i];
-      int rc;
-      if (b.swap) {
-        // each listed qubit to its physical bit, the occupant to its old place
-        std::vector<int32_t> L(static_cast<size_t>(p->n)), Linv(static_cast<size_t>(p->n));
-        rc = sv_get_layout(s, L.data());
-        if (rc) return rc;
-        for (int q = 0; q < p->n; ++q) Linv[size_t(L[size_t(q)])] = q;
-        for (int j = 0; j < b.k; ++j) {
-          const int32_t q = b.tuple[size_t(j)], to = b.dest[size_t(j)], from = L[size_t(q)];
-          if (from == to) continue;
-          const int32_t r = Linv[size_t(to)];
-          L[size_t(q)] = to;
-          L[size_t(r)] = from;
-          Linv[size_t(to)] = q;
-          Linv[size_t(from)] = r;
-        }
-        rc = sv_permute_layout(s, L.data());
-        if (rc) return rc;
-        continue;
-      }
-      rc = sv_hint_next_use(s, hints[i].data());
-      if (rc) return rc;
-      rc = sv_apply_fused(s, b.matrix.data(), b.tuple.data(), b.k);
-      if (rc) return rc;
-    }
     return SV_OK;
   });
 }
