@@ -1,8 +1,11 @@
 // Cost-model MLP: forward, backward and Adam kernels (FP32); the host
 // forward for the planner is in sv_mlp_host.cpp.  Sizes are tiny (5k
-// parameters, batches of a few thousand rows): one thread per output
-// element, reductions over the batch in a fixed order so every run gives
-// the same bits.
+// parameters, batches of a few thousand rows), so a step is bound by latency:
+// launches, and the chain of each sum.  A network of at most 64 inputs and 64
+// hidden units runs a wave per row with the weights in LDS (one launch
+// forward, one for the row part of the backward pass); the sums over the batch
+// take a wave's lane per column and 16 slices of the rows, combined in a
+// fixed order so every run gives the same bits.
 #include <cmath>
 #include <vector>
 
@@ -46,22 +49,167 @@ __global__ __launch_bounds__(kT) void k_out(const float *__restrict__ z2, int hi
   y[r] = acc;
 }
 
-// loss = 0.5 mean (y - t)^2, one workgroup, fixed tree
-__global__ __launch_bounds__(kT) void k_loss(const float *__restrict__ y, const float *__restrict__ t, int batch,
-                                             float *__restrict__ loss) {
-  __shared__ float red[kT];
-  float s = 0.f;
-  for (int r = threadIdx.x; r < batch; r += kT) {
-    const float d = y[r] - t[r];
-    s = fmaf(d, d, s);
-  }
-  red[threadIdx.x] = s;
+// Forward of up to 64 inputs and 64 hidden units: lane u of a wave is hidden
+// unit u of the wave's row; sums run in input order, as in k_dense.
+constexpr int kRowWaves = 4, kRowsPerWave = 4, kMaxUnits = 64;
+__global__ __launch_bounds__(64 * kRowWaves) void k_forward_rows(const float *__restrict__ X, int nin, int hid,
+                                                                 const float *__restrict__ params, Off o, int batch,
+                                                                 float *__restrict__ z1, float *__restrict__ z2,
+                                                                 float *__restrict__ y) {
+  __shared__ float w1[kMaxUnits * kMaxUnits], w2[kMaxUnits * kMaxUnits];
+  __shared__ float row[kRowWaves][kMaxUnits];
+  for (int i = threadIdx.x; i < nin * hid; i += 64 * kRowWaves) w1[i] = params[o.w1 + i];
+  for (int i = threadIdx.x; i < hid * hid; i += 64 * kRowWaves) w2[i] = params[o.w2 + i];
+  const int u = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool on = u < hid;
+  const float b1 = on ? params[o.b1 + u] : 0.f, b2 = on ? params[o.b2 + u] : 0.f;
+  const float w3 = on ? params[o.w3 + u] : 0.f, b3 = params[o.b3];
+  const int uu = on ? u : 0;
   __syncthreads();
-  for (int w = kT / 2; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+  for (int j = 0; j < kRowsPerWave; ++j) {
+    const int r = (int(blockIdx.x) * kRowsPerWave + j) * kRowWaves + wave;
+    const bool live = r < batch;
+    if (live && u < nin) row[wave][u] = X[int64_t(r) * nin + u];
+    __syncthreads();
+    float a = b1;
+#pragma unroll 4
+    for (int i = 0; i < nin; ++i) a = fmaf(row[wave][i], w1[i * hid + uu], a);
+    __syncthreads();
+    row[wave][u] = a > 0.f ? a : 0.f;
+    if (live && on) z1[int64_t(r) * hid + u] = a;
+    __syncthreads();
+    float c = b2;
+#pragma unroll 8
+    for (int i = 0; i < hid; ++i) c = fmaf(row[wave][i], w2[i * hid + uu], c);
+    if (live && on) z2[int64_t(r) * hid + u] = c;
+    float s = (on && c > 0.f) ? c * w3 : 0.f;
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) s += __shfl_xor(s, m);
+    if (live && u == 0) y[r] = s + b3;
     __syncthreads();
   }
-  if (threadIdx.x == 0) *loss = 0.5f * red[0] / float(batch);
+}
+
+// Row part of the backward pass, likewise: dz2 = dy w3 [z2 > 0], then
+// dz1[a] = sum_u dz2[u] W2[a][u] [z1 > 0] with W2's rows a word apart in LDS.
+__global__ __launch_bounds__(64 * kRowWaves) void k_backward_rows(const float *__restrict__ y,
+                                                                  const float *__restrict__ t, int hid,
+                                                                  const float *__restrict__ params, Off o, int batch,
+                                                                  const float *__restrict__ z1,
+                                                                  const float *__restrict__ z2,
+                                                                  float *__restrict__ dz1, float *__restrict__ dz2) {
+  __shared__ float w2[kMaxUnits * (kMaxUnits + 1)];
+  __shared__ float row[kRowWaves][kMaxUnits];
+  for (int i = threadIdx.x; i < hid * hid; i += 64 * kRowWaves)
+    w2[(i / hid) * (kMaxUnits + 1) + i % hid] = params[o.w2 + i];
+  const int u = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const bool on = u < hid;
+  const float w3 = on ? params[o.w3 + u] : 0.f;
+  const int uu = on ? u : 0;
+  __syncthreads();
+  for (int j = 0; j < kRowsPerWave; ++j) {
+    const int r = (int(blockIdx.x) * kRowsPerWave + j) * kRowWaves + wave;
+    const bool live = r < batch && on;
+    const int64_t at = int64_t(r) * hid + u;
+    const float dy = live ? (y[r] - t[r]) / float(batch) : 0.f;
+    const float d2 = live && z2[at] > 0.f ? dy * w3 : 0.f;
+    if (live) dz2[at] = d2;
+    row[wave][u] = d2;
+    __syncthreads();
+    float a = 0.f;
+#pragma unroll 8
+    for (int i = 0; i < hid; ++i) a = fmaf(row[wave][i], w2[uu * (kMaxUnits + 1) + i], a);
+    if (live) dz1[at] = z1[at] > 0.f ? a : 0.f;
+    __syncthreads();
+  }
+}
+
+// Sums over the batch: workgroup x is one gradient row (W2's rows and b2, W1's
+// rows and b1, W3, then b3 and the loss), workgroup y 64 of its columns.  A lane
+// takes a column, a wave one of 16 slices of the rows; the slices meet in LDS
+// in order.  One thread per output over the whole batch (1712 rows) took 414
+// us for each layer and 475 for the output; all of them
+// take 23 us.
+constexpr int kSlices = 16;
+__global__ __launch_bounds__(64 * kSlices) void k_grads(const float *__restrict__ X, int nin, int hid,
+                                                        const float *__restrict__ z1, const float *__restrict__ z2,
+                                                        const float *__restrict__ dz1,
+                                                        const float *__restrict__ dz2, const float *__restrict__ y,
+                                                        const float *__restrict__ t, Off o, int batch,
+                                                        float *__restrict__ grads, float *__restrict__ loss) {
+  __shared__ float red[2][kSlices][64];
+  const int lane = threadIdx.x & 63, slice = threadIdx.x >> 6;
+  const int u = int(blockIdx.y) * 64 + lane;
+  int g = blockIdx.x;
+  const bool last = g == hid + nin + 3;
+  float s = 0.f, q = 0.f;
+  float *out = nullptr;
+  if (g <= hid + nin + 1) {  // a row of a weight matrix, or its bias
+    const bool second = g <= hid;
+    const int i = second ? g : g - (hid + 1), ni = second ? hid : nin;
+    const float *in = second ? z1 : X, *d = second ? dz2 : dz1;
+    out = grads + (i < ni ? (second ? o.w2 : o.w1) + int64_t(i) * hid : int64_t(second ? o.b2 : o.b1));
+    // eight rows at a time, all their loads before the first sum
+    const bool bias = i == ni;
+    const float *xp = in + (bias ? 0 : i), *dp = d + (u < hid ? u : 0);
+    for (int r0 = slice; r0 < batch; r0 += 8 * kSlices) {
+      float x[8], e[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int r = r0 + k * kSlices, rc = r < batch ? r : r0;
+        x[k] = xp[int64_t(rc) * ni];
+        e[k] = dp[int64_t(rc) * hid];
+        if (r >= batch) x[k] = e[k] = 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const float h = second && !(x[k] > 0.f) ? 0.f : x[k];
+        s = fmaf(bias ? 1.f : h, e[k], s);
+      }
+    }
+  } else if (!last) {  // W3
+    out = grads + o.w3;
+    const float *zp = z2 + (u < hid ? u : 0);
+    for (int r0 = slice; r0 < batch; r0 += 8 * kSlices) {
+      float h[8], e[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int r = r0 + k * kSlices, rc = r < batch ? r : r0;
+        h[k] = zp[int64_t(rc) * hid];
+        e[k] = (y[rc] - t[rc]) / float(batch);
+        if (r >= batch) h[k] = e[k] = 0.f;
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s = fmaf(h[k] > 0.f ? h[k] : 0.f, e[k], s);
+    }
+  } else if (blockIdx.y == 0) {  // b3 and the loss: the rows over all threads
+    for (int r = threadIdx.x; r < batch; r += 64 * kSlices) {
+      const float e = y[r] - t[r];
+      s += e / float(batch);
+      q = fmaf(e, e, q);
+    }
+  }
+  red[0][slice][lane] = s;
+  red[1][slice][lane] = q;
+  __syncthreads();
+  if (slice) return;
+  for (int k = 1; k < kSlices; ++k) {
+    s += red[0][k][lane];
+    q += red[1][k][lane];
+  }
+  if (last) {
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) {
+      s += __shfl_xor(s, m);
+      q += __shfl_xor(q, m);
+    }
+    if (lane == 0 && blockIdx.y == 0) {
+      grads[o.b3] = s;
+      *loss = 0.5f * q / float(batch);
+    }
+  } else if (u < hid) {
+    out[u] = s;
+  }
 }
 
 // dz2[r][u] = (y - t)/B * w3[u] * [z2 > 0]
@@ -87,49 +235,6 @@ __global__ __launch_bounds__(kT) void k_dz1(const float *__restrict__ dz2, const
   dz1[idx] = z1[idx] > 0.f ? acc : 0.f;
 }
 
-// gW[i][u] = sum_r act(in[r][i]) d[r][u]; gb[u] = sum_r d[r][u]   (rows i = nin are the bias)
-__global__ __launch_bounds__(kT) void k_wgrad(const float *__restrict__ in, int nin, bool relu_in,
-                                              const float *__restrict__ d, int hid, int batch,
-                                              float *__restrict__ gW, float *__restrict__ gb) {
-  const int idx = blockIdx.x * kT + threadIdx.x;
-  if (idx >= (nin + 1) * hid) return;
-  const int i = idx / hid, u = idx % hid;
-  float acc = 0.f;
-  if (i < nin) {
-    for (int r = 0; r < batch; ++r) {
-      float x = in[int64_t(r) * nin + i];
-      if (relu_in) x = x > 0.f ? x : 0.f;
-      acc = fmaf(x, d[int64_t(r) * hid + u], acc);
-    }
-    gW[i * hid + u] = acc;
-  } else {
-    for (int r = 0; r < batch; ++r) acc += d[int64_t(r) * hid + u];
-    gb[u] = acc;
-  }
-}
-
-// output layer: gW3[u] = sum_r relu(z2[r][u]) dy[r]; gb3 = sum_r dy[r]
-__global__ __launch_bounds__(kT) void k_out_grad(const float *__restrict__ z2, const float *__restrict__ y,
-                                                 const float *__restrict__ t, int hid, int batch,
-                                                 float *__restrict__ gw3, float *__restrict__ gb3) {
-  const int u = blockIdx.x * kT + threadIdx.x;
-  if (u > hid) return;
-  float acc = 0.f;
-  for (int r = 0; r < batch; ++r) {
-    const float dy = (y[r] - t[r]) / float(batch);
-    if (u < hid) {
-      const float h = z2[int64_t(r) * hid + u];
-      acc = fmaf(h > 0.f ? h : 0.f, dy, acc);
-    } else {
-      acc += dy;
-    }
-  }
-  if (u < hid)
-    gw3[u] = acc;
-  else
-    gb3[0] = acc;
-}
-
 __global__ __launch_bounds__(kT) void k_adam(float *__restrict__ p, const float *__restrict__ g,
                                              float *__restrict__ m, float *__restrict__ v, int count, float lr,
                                              float b1, float b2, float eps, float c1, float c2) {
@@ -145,6 +250,10 @@ __global__ __launch_bounds__(kT) void k_adam(float *__restrict__ p, const float 
 }
 
 unsigned blocks(int64_t n) { return unsigned((n + kT - 1) / kT); }
+
+// Networks that fit the row kernels, and their launch.
+bool rows_fit(int nin, int hid) { return nin <= kMaxUnits && hid <= kMaxUnits; }
+unsigned row_blocks(int batch) { return unsigned((int64_t(batch) + kRowWaves * kRowsPerWave - 1) / (kRowWaves * kRowsPerWave)); }
 
 }  // namespace
 }  // namespace sv
@@ -163,6 +272,12 @@ int sv_mlp_forward(const float *params, int nin, int hid, const float *X, int ba
     hipStream_t st = static_cast<hipStream_t>(stream);
     const Off o = offsets(nin, hid);
     float *z1 = cache, *z2 = cache + int64_t(hid) * batch;
+    if (rows_fit(nin, hid)) {
+      hipLaunchKernelGGL(k_forward_rows, dim3(row_blocks(batch)), dim3(64 * kRowWaves), 0, st, X, nin, hid, params, o,
+                         batch, z1, z2, y);
+      SV_HIP_CHECK(hipGetLastError());
+      return SV_OK;
+    }
     hipLaunchKernelGGL(k_dense, dim3(blocks(int64_t(batch) * hid)), dim3(kT), 0, st, X, nin, false, params + o.w1,
                        params + o.b1, hid, batch, z1);
     hipLaunchKernelGGL(k_dense, dim3(blocks(int64_t(batch) * hid)), dim3(kT), 0, st, z1, hid, true, params + o.w2,
@@ -185,17 +300,17 @@ int sv_mlp_backward(const float *params, int nin, int hid, const float *X, const
     const float *z1 = cache, *z2 = cache + int64_t(hid) * batch;
     float *dz2 = const_cast<float *>(cache) + 2 * int64_t(hid) * batch;
     float *dz1 = const_cast<float *>(cache) + 3 * int64_t(hid) * batch;
-    hipLaunchKernelGGL(k_loss, dim3(1), dim3(kT), 0, st, y, target, batch, loss);
-    hipLaunchKernelGGL(k_out_grad, dim3(blocks(hid + 1)), dim3(kT), 0, st, z2, y, target, hid, batch, grads + o.w3,
-                       grads + o.b3);
-    hipLaunchKernelGGL(k_dz2, dim3(blocks(int64_t(batch) * hid)), dim3(kT), 0, st, y, target, z2, params + o.w3, hid,
-                       batch, dz2);
-    hipLaunchKernelGGL(k_wgrad, dim3(blocks((hid + 1) * hid)), dim3(kT), 0, st, z1, hid, true, dz2, hid, batch,
-                       grads + o.w2, grads + o.b2);
-    hipLaunchKernelGGL(k_dz1, dim3(blocks(int64_t(batch) * hid)), dim3(kT), 0, st, dz2, params + o.w2, z1, hid, batch,
-                       dz1);
-    hipLaunchKernelGGL(k_wgrad, dim3(blocks((nin + 1) * hid)), dim3(kT), 0, st, X, nin, false, dz1, hid, batch,
-                       grads + o.w1, grads + o.b1);
+    if (rows_fit(nin, hid)) {
+      hipLaunchKernelGGL(k_backward_rows, dim3(row_blocks(batch)), dim3(64 * kRowWaves), 0, st, y, target, hid, params,
+                         o, batch, z1, z2, dz1, dz2);
+    } else {
+      hipLaunchKernelGGL(k_dz2, dim3(blocks(int64_t(batch) * hid)), dim3(kT), 0, st, y, target, z2, params + o.w3, hid,
+                         batch, dz2);
+      hipLaunchKernelGGL(k_dz1, dim3(blocks(int64_t(batch) * hid)), dim3(kT), 0, st, dz2, params + o.w2, z1, hid, batch,
+                         dz1);
+    }
+    hipLaunchKernelGGL(k_grads, dim3(unsigned(hid + nin + 4), unsigned((hid + 63) / 64)), dim3(64 * kSlices), 0, st, X,
+                       nin, hid, z1, z2, dz1, dz2, y, target, o, batch, grads, loss);
     SV_HIP_CHECK(hipGetLastError());
     return SV_OK;
   });
