@@ -729,54 +729,51 @@ int sv_permute_layout(sv_state *s, const int32_t *new_layout) {
       }
       seen[p] = true;
     }
-    // Selection order (permutation_swaps): fill physical positions 0..n-1
-    // with their final qubits, one bit transposition at a time.  Consecutive
-    // disjoint transpositions commute, so several of them run as one
-    // in-place tile pass (permutation_pass_end) when the state has at least
-    // kPermTileBits qubits; smaller states use single transposition passes.
-    const std::vector<std::pair<int, int>> swaps = permutation_swaps(s->L, new_layout, n);
-    size_t i = 0;
-    while (i < swaps.size()) {
-      if (n < kPermTileBits) {
-        SV_HIP_CHECK(launch_swap_bits(s->amps, n, swaps[i].first, swaps[i].second, s->st));
-        swap_physical(s, swaps[i].first, swaps[i].second);
+    // Small states: single bit transpositions, each half of the state.
+    if (n < kPermTileBits) {
+      for (const std::pair<int, int> &x : permutation_swaps(s->L, new_layout, n)) {
+        SV_HIP_CHECK(launch_swap_bits(s->amps, n, x.first, x.second, s->st));
+        swap_physical(s, x.first, x.second);
         s->stats.swap_half_sweeps += 1;
         s->stats.launches += 1;
-        ++i;
-        continue;
       }
-      const size_t j = permutation_pass_end(swaps, i);
-      uint64_t used = 0;
-      for (size_t t = i; t < j; ++t) used |= (uint64_t(1) << swaps[t].first) | (uint64_t(1) << swaps[t].second);
-      // tile: the exchanged bits plus the lowest other bits, kPermTileBits in all
-      uint64_t smask = used;
-      for (int p = 0; p < n && __builtin_popcountll(smask) < kPermTileBits; ++p) smask |= uint64_t(1) << p;
+      return SV_OK;
+    }
+    // Others: in-place tile passes (permutation_tiles), of the wide tile where
+    // that takes fewer.
+    std::vector<PermPass> passes = permutation_tiles(s->L, new_layout, n, kPermTileBits);
+    int S = kPermTileBits;
+    if (n >= kPermWideBits) {
+      std::vector<PermPass> wide = permutation_tiles(s->L, new_layout, n, kPermWideBits);
+      if (wide.size() < passes.size()) {
+        passes.swap(wide);
+        S = kPermWideBits;
+      }
+    }
+    for (const PermPass &pass : passes) {
       TilePlan tp;
       tp.n = n;
-      tp.s = kPermTileBits;
+      tp.s = S;
       tp.order = s->tile_order;
-      int b = 0;
+      int local[64], b = 0;
       for (int p = 0; p < n; ++p)
-        if ((smask >> p) & 1) {
+        if ((pass.tile >> p) & 1) {
           tp.sbit[b] = p;
           tp.loc_in[b] = b;
-          tp.loc_out[b] = b;
-          ++b;
+          local[p] = b++;
         }
-      for (size_t t = i; t < j; ++t) {
-        int ba = -1, bb = -1;
-        for (int c = 0; c < tp.s; ++c) {
-          if (tp.sbit[c] == swaps[t].first) ba = c;
-          if (tp.sbit[c] == swaps[t].second) bb = c;
-        }
-        tp.loc_out[ba] = bb;
-        tp.loc_out[bb] = ba;
-      }
+      for (int p = 0; p < n; ++p)
+        if ((pass.tile >> p) & 1) tp.loc_out[local[int(pass.to[p])]] = local[p];
       SV_HIP_CHECK(launch_tile_permute(tp, s->amps, s->st));
-      for (size_t t = i; t < j; ++t) swap_physical(s, swaps[t].first, swaps[t].second);
+      int32_t Linv[64];
+      std::memcpy(Linv, s->Linv, sizeof(Linv));
+      for (int p = 0; p < n; ++p)
+        if ((pass.tile >> p) & 1) {
+          s->L[Linv[p]] = pass.to[p];
+          s->Linv[int(pass.to[p])] = Linv[p];
+        }
       s->stats.permute_sweeps += 1;
       s->stats.launches += 1;
-      i = j;
     }
     return SV_OK;
   });

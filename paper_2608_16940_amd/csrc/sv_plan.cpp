@@ -832,7 +832,7 @@ extern "C" int sv_plan_swaps(sv_plan *p, const float *mlp_params, int mlp_nin, i
             }
             if (!c.diag) gain += cost(c, La) - cost(c, Lb);
           }
-          // the tile passes sv_permute_layout will run for this move
+          // passes of five exchanges: at least the tile passes sv_permute_layout runs for this move
           const double price =
               double(sv::permutation_passes(L.data(), L2.data(), n)) * stream * SV_PLAN_SWAP_SWEEP_FACTOR;
           if (gain > price * (1.0 + margin) && gain - price > best) {

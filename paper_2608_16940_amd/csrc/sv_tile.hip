@@ -85,7 +85,7 @@ struct TileArgs {
   int64_t goff_i[32];
   int32_t lam_i[32];
   int32_t lamo_i[32];
-  int32_t pswz[7];  // k_tile_permute: LDS swizzle images of local bits 5..11 (lin_swz)
+  int32_t pswz[8];  // k_tile_permute: LDS swizzle images of local bits 5.. (lin_swz)
 };
 
 __device__ __forceinline__ int64_t insert_zero_bit(int64_t x, int p) {
@@ -561,10 +561,11 @@ __global__ __launch_bounds__((256 * KSplit<K, PREC, OPS>::value), (WavesPerSimd<
 // X is linear over GF(2) (bit 5 + j of l contributes pswz[j] to the low five
 // bits).  The map is a bijection and linear, so the address of a thread's
 // part OR a chunk's part (disjoint bits) is the XOR of the parts' addresses.
+template <int NB>
 __device__ __forceinline__ int lin_swz(int l, const int32_t *px) {
   int x = 0;
 #pragma unroll
-  for (int j = 0; j < 7; ++j) x ^= -((l >> (5 + j)) & 1) & px[j];  // no branches
+  for (int j = 0; j < NB; ++j) x ^= -((l >> (5 + j)) & 1) & px[j];  // no branches
   return l ^ x;
 }
 
@@ -576,23 +577,27 @@ __device__ __forceinline__ int lin_swz(int l, const int32_t *px) {
 // times: one pass ran at 44% of HBM peak).  lam_i / lamo_i hold the chunks'
 // swizzled addresses.
 template <int S>
-__global__ __launch_bounds__(256) void k_tile_permute(TileArgs a) {
-  static_assert(S == 12, "the swizzle covers local bits 5..11");  // kPermTileBits
-  constexpr int NT = 256;
+struct PermThreads {
+  static constexpr int bits = S == 12 ? 8 : 9;  // eight 16-byte chunks per thread
+};
+template <int S>
+__global__ __launch_bounds__((1 << PermThreads<S>::bits)) void k_tile_permute(TileArgs a) {
+  constexpr int TB = PermThreads<S>::bits, NT = 1 << TB, NB = S - 5;
+  static_assert(NB <= 8, "swizzle images of local bits 5 up");
   constexpr int CHUNKS = (1 << (S - 1)) / NT;
   __shared__ float2 lds[1 << S];
   const int t = threadIdx.x;
   int64_t goff_t = 0;
   int lamo_t = 0;
 #pragma unroll
-  for (int b = 1; b <= 8; ++b) {  // without branches, as in k_tile_mfma
+  for (int b = 1; b <= TB; ++b) {  // without branches, as in k_tile_mfma
     const int on = (t >> (b - 1)) & 1;
     goff_t |= int64_t(on) << a.sbit[b];
     lamo_t |= on << a.loc_out[b];
   }
-  const int wr_t = lin_swz(2 * t, a.pswz);   // identity on load: local index 2t + 512 i
-  const int rd_t = lin_swz(lamo_t, a.pswz);
-  const int rd_b = lin_swz(1 << a.lb_out, a.pswz);
+  const int wr_t = lin_swz<NB>(2 * t, a.pswz);   // identity on load: local index 2t + 2 NT i
+  const int rd_t = lin_swz<NB>(lamo_t, a.pswz);
+  const int rd_b = lin_swz<NB>(1 << a.lb_out, a.pswz);
   for (int64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
     int64_t base = tile_of(tile, a.xs);
 #pragma unroll
@@ -604,7 +609,7 @@ __global__ __launch_bounds__(256) void k_tile_permute(TileArgs a) {
     for (int i = 0; i < CHUNKS; ++i) {
       const int l0 = wr_t ^ a.lam_i[i];
       lds[l0] = make_float2(v[i].x, v[i].y);
-      lds[l0 ^ 1] = make_float2(v[i].z, v[i].w);  // X reads bits 5..11 only: f(l ^ 1) = f(l) ^ 1
+      lds[l0 ^ 1] = make_float2(v[i].z, v[i].w);  // X reads bits from 5 up: f(l ^ 1) = f(l) ^ 1
     }
     __syncthreads();
 #pragma unroll
@@ -949,22 +954,29 @@ hipError_t launch_tile_mfma(const TilePlan &tp, int prec, int opsrc, float2 *psi
 // bits 20..23 with 0..3: 4.8 -> 2.9 ms).
 constexpr int kPermuteTileOrder = 9;
 
-hipError_t launch_tile_permute(const TilePlan &tp_in, float2 *psi, hipStream_t st) {
-  constexpr int S = kPermTileBits;
-  if (tp_in.s != S || tp_in.n < S) return hipErrorInvalidValue;
-  constexpr int NT = 256;
-  constexpr int CHUNKS = (1 << (S - 1)) / NT;
-  TilePlan tp = tp_in;
-  if (tp.order < 0) tp.order = kPermuteTileOrder;
+template <int S>
+static hipError_t tile_permute_s(const TilePlan &tp, float2 *psi, hipStream_t st) {
+  constexpr int NT = 1 << PermThreads<S>::bits, CHUNKS = (1 << (S - 1)) / NT;
   TileArgs a;
   fill_args(tp, NT, CHUNKS, psi, nullptr, &a);
-  choose_perm_swizzle(tp.loc_out, a.pswz);
+  choose_perm_swizzle(tp.loc_out, a.pswz, S - 5);
   for (int i = 0; i < CHUNKS; ++i) {
-    a.lam_i[i] = lin_swz_host(a.lam_i[i], a.pswz);
-    a.lamo_i[i] = lin_swz_host(a.lamo_i[i], a.pswz);
+    a.lam_i[i] = lin_swz_host(a.lam_i[i], a.pswz, S - 5);
+    a.lamo_i[i] = lin_swz_host(a.lamo_i[i], a.pswz, S - 5);
   }
   hipLaunchKernelGGL((k_tile_permute<S>), dim3(grid_of(a.ntiles)), dim3(NT), 0, st, a);
   return hipGetLastError();
+}
+
+hipError_t launch_tile_permute(const TilePlan &tp_in, float2 *psi, hipStream_t st) {
+  if (tp_in.n < tp_in.s) return hipErrorInvalidValue;
+  TilePlan tp = tp_in;
+  if (tp.order < 0) tp.order = kPermuteTileOrder;
+  switch (tp.s) {
+    case kPermTileBits: return tile_permute_s<kPermTileBits>(tp, psi, st);
+    case kPermWideBits: return tile_permute_s<kPermWideBits>(tp, psi, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace sv

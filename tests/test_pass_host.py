@@ -1,4 +1,4 @@
-"""The fused-pass builder against gate-by-gate application, on the CPU.
+"""The fused-pass builder against gate-by-gate application, and the layout passes, on the CPU.
 
 tests/native/pass_check.cpp replays the builder's device data in FP64 the way
 the kernel reads it, for n = 1..17 qubits, random targets in any order, gates
@@ -31,3 +31,19 @@ def test_passes_equal_gates_one_by_one():
     r = subprocess.run([exe, "2"], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-6000:])
     assert "pass checks passed" in r.stdout
+
+
+def test_layout_passes_reach_the_target():
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    out = os.path.join(ROOT, "_build")
+    os.makedirs(out, exist_ok=True)
+    exe = os.path.join(out, "perm_check")
+    r = subprocess.run([gxx, "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                        "-I", CSRC, os.path.join(ROOT, "tests", "native", "perm_check.cpp"), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-6000:])
+    assert "permutation checks passed" in r.stdout
