@@ -136,6 +136,9 @@ bool qubit_permutation(const double *G, int k, int *perm);
 hipError_t launch_tile_mfma(const TilePlan &tp, int prec, int opsrc, float2 *psi, const void *operand_dev,
                             hipStream_t st);
 
+// Probabilities in logical order, n >= 12, out 16-byte aligned: reads and writes in runs through LDS tiles.
+hipError_t launch_probs_tile(const float2 *psi, int n, double *out, const LayoutArg &L, hipStream_t st);
+
 // Pure bit permutation within a tile: tp.loc_out describes where each tile bit goes.
 hipError_t launch_tile_permute(const TilePlan &tp, float2 *psi, hipStream_t st);
 

@@ -742,6 +742,12 @@ hipError_t launch_swap_bits(float2 *psi, int n, int p, int q, hipStream_t st) {
 
 hipError_t launch_probs(const float2 *psi, int n, double *out, int logical, const LayoutArg &L, hipStream_t st) {
   const int64_t dim = int64_t(1) << n;
+  bool moved = false;
+  for (int q = 0; q < n; ++q) moved = moved || L.pos[q] != q;
+  if (!moved) logical = 0;  // the identity layout: both orders are one
+  // the tile kernel from 2^12 amplitudes, where it exists, to any; the map per amplitude below and for
+  // an output that 16-byte stores do not fit
+  if (logical && n >= 12 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) return launch_probs_tile(psi, n, out, L, st);
   hipLaunchKernelGGL(k_probs, dim3(grid_for(dim, kThreads, kFullGrid)), dim3(kThreads), 0, st, psi, dim, n, out,
                      logical, L);
   return hipGetLastError();

@@ -50,6 +50,7 @@ namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex2 __attribute__((ext_vector_type(2)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -621,6 +622,67 @@ __global__ __launch_bounds__((1 << PermThreads<S>::bits)) void k_tile_permute(Ti
   }
 }
 
+// Probabilities in logical order from a state in another layout.  Read amplitude
+// by amplitude through the map, every 64-byte line is fetched for 8 bytes (N=28
+// after a QFT, whose layout is reversed: 8.7 ms).  A tile that holds physical
+// bits 0..3 and the bits logical qubits 0..3 sit on reads runs of at least 128
+// bytes in one order and writes runs of at least 128 bytes in the other, the
+// transposition happening in LDS (0.93 ms, 4.6 TB/s of reads and writes).
+struct ProbTileArgs {
+  const float2 *psi;
+  double *out;
+  int64_t ntiles;
+  int n, xs, lb_out;
+  int sbit[kPermTileBits];     // physical tile bits, ascending: local bit b
+  int obit[kPermTileBits];     // their logical bits, ascending: output order
+  int loc_out[kPermTileBits];  // local bit that supplies bit b of the output order
+  int64_t goff_i[8], ooff_i[8];
+  int32_t lam_i[8], lamo_i[8], pswz[8];
+  int8_t lbit[64];  // logical bit at each physical bit
+};
+
+__global__ __launch_bounds__(256) void k_probs_tile(ProbTileArgs a) {
+  constexpr int S = kPermTileBits, NB = S - 5, CHUNKS = (1 << (S - 1)) / 256;
+  __shared__ double lds[1 << S];
+  const int t = threadIdx.x;
+  int64_t goff_t = 0, ooff_t = 0;
+  int lamo_t = 0;
+#pragma unroll
+  for (int b = 1; b <= 8; ++b) {
+    const int on = (t >> (b - 1)) & 1;
+    goff_t |= int64_t(on) << a.sbit[b];
+    ooff_t |= int64_t(on) << a.obit[b];
+    lamo_t |= on << a.loc_out[b];
+  }
+  const int wr_t = lin_swz<NB>(2 * t, a.pswz);
+  const int rd_t = lin_swz<NB>(lamo_t, a.pswz);
+  const int rd_b = lin_swz<NB>(1 << a.lb_out, a.pswz);
+  for (int64_t tile = blockIdx.x; tile < a.ntiles; tile += gridDim.x) {
+    int64_t base = tile_of(tile, a.xs);
+#pragma unroll
+    for (int b = 0; b < S; ++b) base = insert_zero_bit(base, a.sbit[b]);
+    int64_t obase = 0;
+    for (int p = 0; p < a.n; ++p) obase |= ((base >> p) & 1) << a.lbit[p];
+    float4 v[CHUNKS];
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) v[i] = ld_stream(a.psi + base + goff_t + a.goff_i[i]);
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int l0 = wr_t ^ a.lam_i[i];
+      lds[l0] = double(v[i].x) * double(v[i].x) + double(v[i].y) * double(v[i].y);  // exact products, as prob_of
+      lds[l0 ^ 1] = double(v[i].z) * double(v[i].z) + double(v[i].w) * double(v[i].w);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      const int l0 = rd_t ^ a.lamo_i[i];
+      const doublex2 o = {lds[l0], lds[l0 ^ rd_b]};
+      __builtin_nontemporal_store(o, reinterpret_cast<doublex2 *>(a.out + obase + ooff_t + a.ooff_i[i]));
+    }
+    __syncthreads();
+  }
+}
+
 int64_t pdep_host(uint64_t v, const int *sbit, int s) {
   int64_t o = 0;
   for (int b = 0; b < s; ++b)
@@ -977,6 +1039,49 @@ hipError_t launch_tile_permute(const TilePlan &tp_in, float2 *psi, hipStream_t s
     case kPermWideBits: return tile_permute_s<kPermWideBits>(tp, psi, st);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_probs_tile(const float2 *psi, int n, double *out, const LayoutArg &L, hipStream_t st) {
+  constexpr int S = kPermTileBits, NT = 256, CHUNKS = (1 << (S - 1)) / NT;
+  if (n < S || (reinterpret_cast<uintptr_t>(out) & 15)) return hipErrorInvalidValue;
+  ProbTileArgs a;
+  std::memset(&a, 0, sizeof(a));
+  for (int q = 0; q < n; ++q) a.lbit[int(L.pos[q])] = int8_t(q);
+  // physical bits 0..3 and the bits of logical 0..3, then the lowest of both in turn
+  uint64_t t = 0;
+  for (int b = 0; b < 4; ++b) t |= (uint64_t(1) << b) | (uint64_t(1) << L.pos[b]);
+  for (int b = 4; b < n; ++b) {
+    if (__builtin_popcountll(t) < S) t |= uint64_t(1) << b;
+    if (__builtin_popcountll(t) < S) t |= uint64_t(1) << L.pos[b];
+  }
+  int s = 0, o = 0, local[64], loc_in[S];
+  for (int p = 0; p < n; ++p)
+    if ((t >> p) & 1) {
+      a.sbit[s] = p;
+      loc_in[s] = s;
+      local[p] = s++;
+    }
+  for (int q = 0; q < n; ++q)
+    if ((t >> L.pos[q]) & 1) {
+      a.obit[o] = q;
+      a.loc_out[o++] = local[int(L.pos[q])];
+    }
+  a.psi = psi;
+  a.out = out;
+  a.n = n;
+  a.ntiles = int64_t(1) << (n - S);
+  a.xs = n - S < kPermuteTileOrder + 3 ? 0 : kPermuteTileOrder;
+  a.lb_out = a.loc_out[0];
+  choose_perm_swizzle(a.loc_out, a.pswz, S - 5);
+  for (int i = 0; i < CHUNKS; ++i) {
+    const uint64_t v = uint64_t(2) * uint64_t(i) * uint64_t(NT);
+    a.goff_i[i] = pdep_host(v, a.sbit, S);
+    a.ooff_i[i] = pdep_host(v, a.obit, S);
+    a.lam_i[i] = lin_swz_host(lam_host(v, loc_in, S), a.pswz, S - 5);
+    a.lamo_i[i] = lin_swz_host(lam_host(v, a.loc_out, S), a.pswz, S - 5);
+  }
+  hipLaunchKernelGGL(k_probs_tile, dim3(grid_of(a.ntiles)), dim3(NT), 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace sv

@@ -1,4 +1,4 @@
-"""Layout moves in tile passes, element by element: the smallest
+"""Layout moves in tile passes and probabilities in logical order, element by element: the smallest
 states of each tile, odd sizes and layouts whose low bits go far."""
 import numpy as np
 import pytest
@@ -37,4 +37,17 @@ def test_layout_moves_every_amplitude(n):
         sv.permute_layout(layout)
         assert np.array_equal(sv.layout(), layout)
         assert torch.equal(sv.amps, before[logical_index(n, layout)]), (n, layout)
+    sv.close()
+
+
+@pytest.mark.parametrize("n", [11, 12, 13, 18, 24])
+def test_logical_probabilities_are_exact(n):
+    import torch
+    rng = np.random.default_rng(100 + n)
+    sv = state(n, n)
+    amps = torch.view_as_real(sv.amps).double()
+    want = amps[:, 0] * amps[:, 0] + amps[:, 1] * amps[:, 1]
+    for layout in (np.arange(n)[::-1].copy(), rng.permutation(n), np.roll(np.arange(n), 5), np.arange(n)):
+        sv.permute_layout(layout)
+        assert torch.equal(sv.probs(logical=True), want)
     sv.close()
