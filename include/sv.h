@@ -92,6 +92,19 @@ int sv_reset(sv_state *s);
 int sv_apply_fused(sv_state *s, const double *matrix, const int32_t *targets, int k);
 
 /*
+ * Apply a list of gates in order, as sv_apply_fused one by one: same state up
+ * to rounding, same layout, same statistics apart from launches, and on an
+ * error the gates before the failing one are applied.  With default options
+ * (in either arithmetic) one-qubit gates and diagonals on one or two qubits
+ * that follow each other share passes over the state.
+ *   ks        count gate widths
+ *   targets   the gates' targets one after the other
+ *   matrices  the gates' matrices one after the other; copied before return
+ * Errors: as sv_apply_fused.
+ */
+int sv_apply_gates(sv_state *s, int64_t count, const int32_t *ks, const int32_t *targets, const double *matrices);
+
+/*
  * Physically move amplitudes so that the layout map becomes new_layout
  * (a bijection logical -> physical bit, host int32[N]).  The identity
  * canonicalises the state (the "request materialisation" consumer of

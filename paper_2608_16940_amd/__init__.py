@@ -6,7 +6,9 @@ stream.
 """
 from __future__ import annotations
 
+import array
 import ctypes
+import itertools
 
 import numpy as np
 
@@ -30,6 +32,23 @@ def _stream_ptr(stream):
     if stream is None:
         stream = torch.cuda.current_stream()
     return ctypes.c_void_p(int(stream.cuda_stream)), stream
+
+
+def _gate_list(gates):
+    """Arguments of sv_apply_gates, or None for a list that is not one complex matrix of
+    2^k x 2^k and k integers per gate (applied one by one, so that what precedes a bad gate acts)."""
+    try:
+        targets = [g.targets for g in gates]
+        ks = [len(t) for t in targets]
+        matrices = [np.ascontiguousarray(g.matrix, np.complex128) for g in gates]
+        if [m.size for m in matrices] != [1 << (2 * k) for k in ks]:
+            return None
+        ks = array.array("i", ks)
+        flat = array.array("i", itertools.chain.from_iterable(targets))
+    except (TypeError, ValueError, OverflowError, AttributeError):
+        return None
+    # the library copies what it needs before it returns
+    return len(gates), bytes(ks), bytes(flat), b"".join(matrices)
 
 
 class StateVector:
@@ -80,6 +99,12 @@ class StateVector:
                                    int(t.size)))
 
     def apply_gates(self, gates):
+        """The gates (objects with ``matrix`` and ``targets``) in order, as ``apply`` one by one."""
+        if isinstance(gates, (list, tuple)) and type(self).apply is StateVector.apply:
+            call = _gate_list(gates)
+            if call is not None:
+                check(lib().sv_apply_gates(self._h, *call))
+                return
         for g in gates:
             self.apply(g.matrix, g.targets)
 

@@ -70,6 +70,7 @@ SIGNATURES = [
     ("sv_free", ctypes.c_int, [_vp]),
     ("sv_reset", ctypes.c_int, [_vp]),
     ("sv_apply_fused", ctypes.c_int, [_vp, _dp, _i32p, ctypes.c_int]),
+    ("sv_apply_gates", ctypes.c_int, [_vp, ctypes.c_int64, _vp, _vp, _vp]),
     ("sv_permute_layout", ctypes.c_int, [_vp, _i32p]),
     ("sv_get_layout", ctypes.c_int, [_vp, _i32p]),
     ("sv_probs", ctypes.c_int, [_vp, _vp, ctypes.c_int]),

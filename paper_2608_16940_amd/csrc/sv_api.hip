@@ -15,6 +15,7 @@
 #include "sv_permute_host.h"
 #include "sv_internal.h"
 #include "sv_pass.h"
+#include "sv_prog.h"
 #include "sv_plan.h"
 #include "sv_plan_types.h"
 
@@ -442,60 +443,65 @@ bool is_diagonal(const double *m, int k) {
   return true;
 }
 
+// Resolves a valid gate from layout L on, as sv_apply_fused would: false when
+// it leaves no work on the state (a qubit permutation, which L takes up, or
+// the identity).  Adds what the gate adds to the statistics.
+bool resolve_gate(int n, const SeqGate &g, int32_t *L, sv_stats *add, pass::Item *it) {
+  int perm[SV_MAX_K];
+  if (qubit_permutation(g.m, g.k, perm)) {
+    int32_t old[SV_MAX_K];
+    for (int j = 0; j < g.k; ++j) old[j] = L[g.t[j]];
+    for (int j = 0; j < g.k; ++j) L[g.t[perm[j]]] = old[j];
+    add->layout_only += 1;
+    return false;
+  }
+  it->k = g.k;
+  it->m = g.m;
+  for (int j = 0; j < g.k; ++j) it->A[j] = L[g.t[j]];
+  it->diag = is_diagonal(g.m, g.k);
+  add->gate_sweeps += 1;
+  int v = SV_VARIANT_GENERIC;  // the lowering the gate has on its own
+  if (it->diag) {
+    v = SV_VARIANT_DIAG;
+    const int D = 1 << g.k;
+    it->exact = true;
+    double dd[512];
+    for (int r = 0; r < D; ++r) {
+      dd[2 * r] = g.m[2 * (size_t(r) * D + r)];
+      dd[2 * r + 1] = g.m[2 * (size_t(r) * D + r) + 1];
+      const double re = std::fabs(dd[2 * r]), im = std::fabs(dd[2 * r + 1]);
+      it->exact = it->exact && ((re == 1.0 && im == 0.0) || (re == 0.0 && im == 1.0));
+    }
+    const DiagCover cv = diag_cover(g.k, dd, it->A);
+    it->sweep = double(cv.nsub) * kDiagLaunchCost;
+    for (int i = 0; i < cv.nsub; ++i) {
+      const int f = __builtin_popcount(cv.mask[i]);
+      it->sweep += std::ldexp(1.0, -f);
+      add->diag_chunks += (int64_t(1) << (n - 1)) >> f;
+    }
+    add->by_variant[v] += 1;
+    return cv.nsub != 0;
+  }
+  it->exact = false;
+  it->sweep = 1.0;
+  if (g.k == 1 && it->A[0] <= 6)
+    v = SV_VARIANT_SHUFFLE;
+  else if (g.k >= 4 && g.k <= 7 && n >= g.k + mfma_tile_M(g.k))
+    v = SV_VARIANT_MFMA;
+  else if (g.k <= 4)
+    v = SV_VARIANT_VALU;
+  add->by_variant[v] += 1;
+  return true;
+}
+
 // Resolves the gates from layout L on and cuts them into steps; every gate valid.
 void plan_sequence(const sv_state *s, const std::vector<SeqGate> &gates, const int32_t *L0, Sequence *q) {
-  const int n = s->n;
   std::memset(&q->add, 0, sizeof(q->add));
   std::memcpy(q->Lend, L0, sizeof(q->Lend));
-  int32_t *L = q->Lend;
-  for (const SeqGate &g : gates) {
-    int perm[SV_MAX_K];
-    if (qubit_permutation(g.m, g.k, perm)) {  // as sv_apply_fused
-      int32_t old[SV_MAX_K];
-      for (int j = 0; j < g.k; ++j) old[j] = L[g.t[j]];
-      for (int j = 0; j < g.k; ++j) L[g.t[perm[j]]] = old[j];
-      q->add.layout_only += 1;
-      continue;
-    }
-    pass::Item it;
-    it.k = g.k;
-    it.m = g.m;
-    for (int j = 0; j < g.k; ++j) it.A[j] = L[g.t[j]];
-    it.diag = is_diagonal(g.m, g.k);
-    q->add.gate_sweeps += 1;
-    int v = SV_VARIANT_GENERIC;  // the lowering the gate has on its own
-    if (it.diag) {
-      v = SV_VARIANT_DIAG;
-      const int D = 1 << g.k;
-      it.exact = true;
-      double dd[512];
-      for (int r = 0; r < D; ++r) {
-        dd[2 * r] = g.m[2 * (size_t(r) * D + r)];
-        dd[2 * r + 1] = g.m[2 * (size_t(r) * D + r) + 1];
-        const double re = std::fabs(dd[2 * r]), im = std::fabs(dd[2 * r + 1]);
-        it.exact = it.exact && ((re == 1.0 && im == 0.0) || (re == 0.0 && im == 1.0));
-      }
-      const DiagCover cv = diag_cover(g.k, dd, it.A);
-      it.sweep = double(cv.nsub) * kDiagLaunchCost;
-      for (int i = 0; i < cv.nsub; ++i) {
-        const int f = __builtin_popcount(cv.mask[i]);
-        it.sweep += std::ldexp(1.0, -f);
-        q->add.diag_chunks += (int64_t(1) << (n - 1)) >> f;
-      }
-      q->add.by_variant[v] += 1;
-      if (cv.nsub == 0) continue;  // the identity
-    } else {
-      if (g.k == 1 && it.A[0] <= 6)
-        v = SV_VARIANT_SHUFFLE;
-      else if (g.k >= 4 && g.k <= 7 && n >= g.k + mfma_tile_M(g.k))
-        v = SV_VARIANT_MFMA;
-      else if (g.k <= 4)
-        v = SV_VARIANT_VALU;
-      q->add.by_variant[v] += 1;
-    }
-    q->items.push_back(it);
-  }
-  q->steps = pass::build_steps(n, q->items, s->prec);
+  pass::Item it;
+  for (const SeqGate &g : gates)
+    if (resolve_gate(s->n, g, q->Lend, &q->add, &it)) q->items.push_back(it);
+  q->steps = pass::build_steps(s->n, q->items, s->prec);
 }
 
 void finish_sequence(sv_state *s, const Sequence &q, const std::vector<SeqGate> &gates) {
@@ -564,6 +570,62 @@ int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
   add_stats(&s->stats, q.add);
   finish_sequence(s, q, gates);
   return SV_OK;
+}
+
+// Runs a list of valid gates in order (sv_apply_gates on a fusible handle):
+// narrow gates in a row share program passes (sv_prog_host.h), any other gate
+// has its own sweep.
+int run_list(sv_state *s, const std::vector<SeqGate> &gates) {
+  sv_stats total = s->stats;
+  std::vector<pass::Item> run;
+  std::vector<prog::Step> steps;
+  auto single = [&](const pass::Item &it) {
+    const int64_t l0 = s->stats.launches;
+    const int rc = apply_physical(s, it.m, it.A, it.k);
+    total.launches += s->stats.launches - l0;
+    return rc;
+  };
+  auto flush = [&]() -> int {
+    if (run.empty()) return SV_OK;
+    steps.clear();
+    prog::build(s->n, run, &steps);
+    for (const prog::Step &x : steps) {
+      if (!x.fused) {
+        for (int i : x.items) {
+          const int rc = single(run[size_t(i)]);
+          if (rc) return rc;
+        }
+        continue;
+      }
+      const hipError_t e = prog::launch(x.args, s->amps, s->st);
+      if (e != hipSuccess) {
+        set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
+        return SV_ERR_DEVICE;
+      }
+      total.launches += 1;
+    }
+    run.clear();
+    return SV_OK;
+  };
+  pass::Item it;
+  int rc = SV_OK;
+  for (const SeqGate &g : gates) {
+    const bool work = resolve_gate(s->n, g, s->L, &total, &it);
+    for (int j = 0; j < g.k; ++j) s->Linv[s->L[g.t[j]]] = g.t[j];
+    ++s->clock;
+    for (int j = 0; j < g.k; ++j) s->last_use[g.t[j]] = s->clock;
+    if (!work) continue;
+    if (s->n >= prog::kMinQubits && prog::takes(it)) {
+      run.push_back(it);
+      continue;
+    }
+    rc = flush();
+    if (rc == SV_OK) rc = single(it);
+    if (rc) break;
+  }
+  if (rc == SV_OK) rc = flush();
+  s->stats = total;
+  return rc;
 }
 
 }  // namespace
@@ -710,6 +772,33 @@ int sv_apply_fused(sv_state *s, const double *matrix, const int32_t *targets, in
       for (int j = 0; j < k; ++j) s->last_use[targets[j]] = s->clock;
     }
     return rc;
+  });
+}
+
+int sv_apply_gates(sv_state *s, int64_t count, const int32_t *ks, const int32_t *targets, const double *matrices) {
+  return guard([&]() -> int {
+    if (!s || count < 0 || (count && (!ks || !targets || !matrices))) {
+      set_error("null pointer or negative count");
+      return SV_ERR_ARG;
+    }
+    const bool fuse = fusible(s);
+    std::vector<SeqGate> gates;
+    if (fuse) gates.reserve(size_t(count));
+    for (int64_t i = 0; i < count; ++i) {
+      const int k = ks[i];
+      const bool ok = valid_targets(s->n, targets, k);
+      if (fuse && ok) {
+        gates.push_back({matrices, targets, k});
+      } else {
+        int rc = run_list(s, gates);  // what precedes an invalid gate is applied
+        gates.clear();
+        if (rc == SV_OK) rc = sv_apply_fused(s, matrices, targets, k);
+        if (rc) return rc;
+      }
+      targets += k;
+      matrices += size_t(2) << (2 * k);
+    }
+    return run_list(s, gates);
   });
 }
 

@@ -47,3 +47,20 @@ def test_layout_passes_reach_the_target():
     r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-6000:])
     assert "permutation checks passed" in r.stdout
+
+
+def test_programs_equal_gates_one_by_one():
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    out = os.path.join(ROOT, "_build")
+    os.makedirs(out, exist_ok=True)
+    exe = os.path.join(out, "prog_check")
+    r = subprocess.run([gxx, "-std=c++17", "-O2", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                        "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                        os.path.join(ROOT, "tests", "native", "prog_check.cpp"),
+                        os.path.join(CSRC, "sv_prog_host.cpp"), "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-6000:])
+    assert "program checks passed" in r.stdout
