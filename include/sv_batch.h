@@ -1,6 +1,6 @@
 /*
- * libsv batched path: many small independent circuits in one persistent
- * kernel launch (an addition to the paper's method, which applies one state
+ * libsv batched path: many small independent circuits in a few launches (one,
+ * and one more per pass of the largest circuits; an addition to the paper's method, which applies one state
  * at a time through the fused-operator interface of Section III R2; the gate
  * semantics are the same).
  *
@@ -67,9 +67,8 @@ int sv_batch_run(int count, const sv_batch_circuit *circs, void *states_dev, siz
  * The same launch split in two, so that repeated runs of one batch (new
  * states each time, same circuits) do no host work: sv_batch_prepare packs
  * the circuits on the host and copies the records into ws_dev (complete
- * before return); sv_batch_launch resets the queue, runs the persistent
- * kernel on `stream` and, if z0_host is not NULL, copies <Z_0> per circuit
- * there and synchronises.  The prepared object refers to ws_dev and the
+ * before return); sv_batch_launch runs the batch's kernels on `stream` and,
+ * if z0_host is not NULL, copies <Z_0> per circuit there and synchronises.  The prepared object refers to ws_dev and the
  * state offsets given at preparation: keep ws_dev alive and unchanged.
  */
 typedef struct sv_batch_prepared sv_batch_prepared;
@@ -93,7 +92,9 @@ int sv_batch_prepared_free(sv_batch_prepared *p);
  *                           single-qubit gates on distinct qubits that the
  *                           kernel applies in one sweep (runs of consecutive
  *                           single-qubit records, grouped by the host)
- *   kind SV_BATCH_GATE_LINEAR (only inside passes) a run of q0 >= 3
+ *   kind SV_BATCH_GATE_LINEAR (only inside passes; the kernel gets such
+ *                           runs of smaller circuits merged too, this call
+ *                           lists their CNOTs) a run of q0 >= 3
  *                           consecutive CNOTs as one linear map f on the 14
  *                           slice bits: the slice becomes new[y] = old[f(y)],
  *                           f(y) the XOR of mask[b] over the set bits b of y;

@@ -1,4 +1,4 @@
-"""Batched small circuits through libsv's persistent kernel (argument marshalling only)."""
+"""Batched small circuits through libsv's batched kernels (argument marshalling only)."""
 from __future__ import annotations
 
 import ctypes

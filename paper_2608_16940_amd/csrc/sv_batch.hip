@@ -1,12 +1,15 @@
-// Batched persistent kernel: thousands of small independent circuits in one
-// launch.  Each workgroup (512 threads) takes packs from an atomic queue; a
-// pack is P circuits with the same qubit count and gate structure, run in
-// lockstep by 512/P threads each.  States of up to 2^14 amplitudes per slice
-// live in LDS from |0...0> to the final write-back.  Larger states run as
-// passes: a pass names the 14 qubits a 2^14-amplitude LDS slice holds and the
-// gates that act only on them; every slice of the state is gathered into LDS,
-// gets all of the pass's gates, and is written back (one read and one write
-// of the state per pass instead of one per gate).
+// Batched small circuits.  The first launch's workgroups (512 threads) each take
+// a pack: P circuits with the same qubit count, run in lockstep by 512/P threads
+// each.  States of up to 2^14 amplitudes per slice live in LDS from |0...0> to
+// the final write-back.  Larger states run as passes: a pass names the 14
+// qubits a 2^14-amplitude LDS slice holds and the gates that act only on them;
+// every slice of the state is gathered into LDS, gets all of the pass's gates,
+// and is written back (one read and one write of the state per pass instead of
+// one per gate).  A pass is a launch: the p-th pass of all such circuits, their
+// slices spread over all CUs.  (With a circuit's slices in turn on one
+// workgroup, the longest circuit held the batch up: 512 circuits of 10..18
+// qubits and 4..12 layers took 5.4 ms, now 1.16 ms; the vector units' share at
+// 64 multiply-adds per CU and clock is 0.42 ms.)
 #include <algorithm>
 #include <atomic>
 #include <climits>
@@ -27,6 +30,26 @@ namespace {
 
 using namespace batch;
 
+
+// Gate records.  Wave-uniform ones are read through the constant address space
+// (scalar loads); the others, of packs with several circuits in a wave,
+// through the global one.  A plain pointer made every read a flat load, one
+// per lane and matrix element.
+typedef const BGate __attribute__((address_space(4))) *UniGates;
+typedef const BGate __attribute__((address_space(1))) *LaneGates;
+__device__ __forceinline__ float hold(UniGates, float x) {
+  asm("" : "+s"(x));
+  return x;
+}
+__device__ __forceinline__ float hold(LaneGates, float x) {
+  asm("" : "+v"(x));
+  return x;
+}
+__device__ __forceinline__ UniGates uniform(const BGate *p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  return (UniGates)((uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(v >> 32)))) << 32) |
+                    uint32_t(__builtin_amdgcn_readfirstlane(int(v & 0xffffffffu))));
+}
 
 // x with a zero bit inserted at position p (LDS indices: states and slices of
 // at most 2^14 amplitudes)
@@ -54,8 +77,9 @@ __device__ __forceinline__ float2 cmad(float ar, float ai, float2 x, float2 acc)
 __device__ __forceinline__ int rot_shift(int lowest_qubit) { return lowest_qubit < 6 ? lowest_qubit : 6; }
 
 // One CNOT on a state of `dim` amplitudes at st (LDS or global), threads lt of Tc.
-__device__ __forceinline__ void apply_cnot(const BGate &G, float2 *st, int dim, int lt, int Tc) {
-  const int cq = G.q0, tq = G.q1;
+template <typename G1>
+__device__ __forceinline__ void apply_cnot(G1 G, float2 *st, int dim, int lt, int Tc) {
+  const int cq = G->q0, tq = G->q1;
   const int lo = cq < tq ? cq : tq, hi = cq < tq ? tq : cq;
   const int s = rot_shift(lo);
   for (int p = lt; p < dim / 4; p += Tc) {
@@ -74,11 +98,13 @@ __device__ __forceinline__ void apply_cnot(const BGate &G, float2 *st, int dim, 
 // amplitude instead of c).
 // The 2x2 factors of a group on the 2^C amplitudes a lane holds (element t
 // holds amplitude t ^ r of its group).
-template <int C>
-__device__ __forceinline__ void group_factors(const BGate *M, int r, float2 *a) {
+template <int C, typename GP>
+__device__ __forceinline__ void group_factors(GP M, int r, float2 *a) {
 #pragma unroll
   for (int j = 0; j < C; ++j) {
-    const float *m = M[j].m;
+    float m[8];  // all eight first: a select between two loads would become a load at a selected address
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m[e] = hold(M, M[j].m[e]);
     const bool sw = (r >> j) & 1;  // this lane holds qubit j's pairs swapped
     const float m0 = sw ? m[6] : m[0], m1 = sw ? m[7] : m[1], m2 = sw ? m[4] : m[2], m3 = sw ? m[5] : m[3];
     const float m4 = sw ? m[2] : m[4], m5 = sw ? m[3] : m[5], m6 = sw ? m[0] : m[6], m7 = sw ? m[1] : m[7];
@@ -98,8 +124,8 @@ __device__ __forceinline__ void group_factors(const BGate *M, int r, float2 *a) 
 }
 
 // Qubits of a group's members, ascending, and their bits.
-template <int C>
-__device__ __forceinline__ void group_qubits(const BGate *M, int *qs, int *srt, int *qbit) {
+template <int C, typename GP>
+__device__ __forceinline__ void group_qubits(GP M, int *qs, int *srt, int *qbit) {
 #pragma unroll
   for (int j = 0; j < C; ++j) {
     qs[j] = srt[j] = M[j].q0;
@@ -116,11 +142,12 @@ __device__ __forceinline__ void group_qubits(const BGate *M, int *qs, int *srt, 
       }
 }
 
-template <int C>
-__device__ __forceinline__ void apply_group_c(const BGate *M, float2 *st, int dim, int lt, int Tc) {
+template <int C, typename GP>
+__device__ __forceinline__ void apply_group_c(GP M, float2 *st, int dim, int lt, int Tc) {
   int qs[C], srt[C], qbit[C];
   group_qubits<C>(M, qs, srt, qbit);
   const int s = rot_shift(srt[0]);
+#pragma unroll 2
   for (int p = lt; p < (dim >> C); p += Tc) {
     int base = p;
 #pragma unroll
@@ -158,7 +185,8 @@ __device__ __forceinline__ void apply_group_c(const BGate *M, float2 *st, int di
 // b of y.  The 14 masks ride in the float slots of the record and of the one
 // after it.  Every thread gathers its 32 amplitudes, the workgroup meets a
 // barrier, then every thread writes them back: one LDS sweep for the run.
-__device__ __forceinline__ void apply_linear(const BGate *R, float2 *lds, int tid) {
+template <typename GP>
+__device__ __forceinline__ void apply_linear(GP R, float2 *lds, int tid) {
   constexpr int PER = kLdsAmps / kBT;  // 32 amplitudes per thread: y = tid + kBT * i
   int32_t mk[kSliceBits];
 #pragma unroll
@@ -194,7 +222,8 @@ static_assert(kLdsAmps == kBT << 5 && kSliceBits == 14, "linear records assume 2
 // maps to f(base) ^ f(o), so f(o) is the XOR of the masks of o's bits.
 // Passes hold kLdsAmps = 2^14 amplitudes over kBT = 512 threads: 2^14 / 2^5
 // groups, one per thread, so every thread meets the barrier once.
-__device__ __forceinline__ void apply_linear_group5(const BGate *RL, const BGate *M, float2 *lds, int tid) {
+template <typename GP>
+__device__ __forceinline__ void apply_linear_group5(GP RL, GP M, float2 *lds, int tid) {
   constexpr int C = 5;
   static_assert((kLdsAmps >> C) == kBT, "one five-qubit group per thread of a pass");
   int32_t mk[kSliceBits];
@@ -254,10 +283,10 @@ __device__ __forceinline__ void apply_linear_group5(const BGate *RL, const BGate
 // amplitudes; returns the number of records it spans.  MAXC: the widest
 // group the caller's records hold (the host groups at most kMaxGroupLds
 // gates for states in LDS and kMaxGroupPass inside passes).
-template <int MAXC>
-__device__ __forceinline__ int apply_unit(const BGate *R, float2 *st, int dim, int lt, int Tc) {
-  if (R[0].kind == SV_BATCH_GATE_LINEAR) {
-    apply_linear(R, st, lt);  // only in passes: dim = kLdsAmps, Tc = kBT
+template <int MAXC, typename GP>
+__device__ __forceinline__ int apply_unit(GP R, float2 *st, int dim, int lt, int Tc) {
+  if (MAXC == kMaxGroupPass && R[0].kind == SV_BATCH_GATE_LINEAR) {
+    apply_linear(R, st, lt);  // dim = kLdsAmps, Tc = kBT; states in LDS: gather_linear
     return 2;
   }
   if (R[0].kind == SV_BATCH_GATE_GROUP) {
@@ -271,194 +300,362 @@ __device__ __forceinline__ int apply_unit(const BGate *R, float2 *st, int dim, i
   if (R[0].kind == SV_BATCH_GATE_1Q)
     apply_group_c<1>(R, st, dim, lt, Tc);
   else if (R[0].kind == SV_BATCH_GATE_CNOT)
-    apply_cnot(R[0], st, dim, lt, Tc);
+    apply_cnot(R, st, dim, lt, Tc);
   return 1;
 }
 static_assert(kMaxGroupLds == 4 && kMaxGroupPass == 5, "the kernel instantiates groups of 2..5");
 
-__global__ void k_batch_reset(unsigned *counter) {
-  if (threadIdx.x == 0) *counter = 0u;
+// A linear record on a state of `dim` amplitudes in LDS that Tc threads hold
+// (up to 32 amplitudes each: y = lt + Tc i): the amplitudes each thread's
+// positions get.  The caller puts a barrier before they are written.
+template <typename GP>
+__device__ __forceinline__ void gather_linear(GP R, const float2 *st, int dim, int lt, int Tc, float2 (&v)[32]) {
+  auto mask = [&](int b) { return b < kSliceBits ? __float_as_int(b < 8 ? R[0].m[b & 7] : R[1].m[(b - 8) & 7]) : 0; };
+  const int tb = 31 - __clz(Tc);
+  int ft = 0;
+  for (int b = 0; b < tb; ++b)
+    if ((lt >> b) & 1) ft ^= mask(b);
+  int mk[5];
+#pragma unroll
+  for (int b = 0; b < 5; ++b) mk[b] = mask(tb + b);
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    int fi = ft;
+#pragma unroll
+    for (int b = 0; b < 5; ++b)
+      if ((i >> b) & 1) fi ^= mk[b];
+    if (lt + Tc * i < dim) v[i] = st[fi];
+  }
 }
 
-__global__ __launch_bounds__(kBT) void k_batch(const BItem *__restrict__ items, int nitems,
-                                               const BGate *__restrict__ gates, float2 *__restrict__ states,
-                                               double *__restrict__ z0, unsigned *__restrict__ counter) {
-  __shared__ float2 lds[kLdsAmps];
-  __shared__ double red[kBT];
-  __shared__ int32_t offlo[128], offhi[128];  // slice index -> state offset, low and high 7 bits
-  __shared__ int item_s;
-  const int tid = threadIdx.x;
-  while (true) {
-    if (tid == 0) item_s = int(atomicAdd(counter, 1u));
-    __syncthreads();
-    const int it = item_s;
-    __syncthreads();  // every thread has read item_s before it is overwritten
-    if (it >= nitems) break;  // uniform: all waves leave together
-    const BItem &I = items[it];
-    const int n = I.n, P = I.P, ngates = I.ngates;
-    const int Tc = kBT / P;
-    const int c = tid / Tc, lt = tid % Tc;
-    const int64_t dim = int64_t(1) << n;
-    const bool in_lds = int64_t(P) * dim <= kLdsAmps;
-    // the LDS state is addressed through the shared array itself, so that its
-    // accesses compile to LDS instructions (a pointer that may also point to
-    // global memory makes every access a flat one)
-    float2 *const sl = lds + (in_lds ? int64_t(c) * dim : 0);
-    float2 *const sg = states + I.state_off[c];
-    const BGate *gl = gates + I.gate_off[c];
-    const int my_ng = I.ngc[c];
+struct Shared {
+  float2 lds[kLdsAmps];
+  double red[kBT];
+  int32_t offlo[128], offhi[128];  // slice index -> state offset, low and high 7 bits
+};
 
-    if (in_lds) {
-      for (int64_t x = lt; x < dim; x += Tc) sl[x] = make_float2(x == 0 ? 1.f : 0.f, 0.f);
+// Slice bit j (j = 0..13) is the j-th lowest qubit of the pass's mask.
+__device__ __forceinline__ void slice_tables(uint32_t mask, int n, int32_t *offlo, int32_t *offhi) {
+  const int tid = threadIdx.x;
+  if (tid >= 256) return;
+  const int half = tid >> 7, v = tid & 127;
+  int32_t off = 0;
+  int j = 0;
+  for (int q = 0; q < n; ++q) {
+    if (!((mask >> q) & 1u)) continue;
+    const int jj = j - 7 * half;
+    if (jj >= 0 && jj < 7 && ((v >> jj) & 1)) off |= int32_t(1) << q;
+    ++j;
+  }
+  (half ? offhi : offlo)[v] = off;
+}
+__device__ __forceinline__ int32_t slice_base(uint32_t mask, int n, int si) {
+  int32_t b = 0;
+  for (int q = 0, r = 0; q < n; ++q) {
+    if ((mask >> q) & 1u) continue;
+    b |= ((si >> r) & 1) << q;
+    ++r;
+  }
+  return b;
+}
+
+// The cnt records of a pass (behind its record M) on the slice in LDS.
+__device__ __forceinline__ void run_pass(UniGates M, int cnt, float2 *lds) {
+  const int tid = threadIdx.x;
+  for (int j = 1; j <= cnt;) {
+    const UniGates R = M + j;
+    if (R[0].kind == SV_BATCH_GATE_LINEAR && j + 2 <= cnt && R[2].kind == SV_BATCH_GATE_GROUP && R[2].q0 == 5) {
+      apply_linear_group5(R, R + 3, lds, tid);  // its members follow the header inside the pass
+      j += 2 + 1 + 5;
     } else {
-      for (int64_t x = lt; x < dim; x += Tc) sg[x] = make_float2(x == 0 ? 1.f : 0.f, 0.f);
+      j += apply_unit<kMaxGroupPass>(R, lds, kLdsAmps, tid, kBT);
     }
-    __syncthreads();
-    if (in_lds) {
-      // lockstep over the pack, one unit (gate or group) per step: a circuit
-      // past its last unit only meets the barriers
-      int r = 0;  // this circuit's next record
-      for (int g = 0; g < ngates; ++g) {
-        if (g < my_ng) r += apply_unit<kMaxGroupLds>(gl + r, sl, int(dim), lt, Tc);
-        __syncthreads();
-      }
-    } else {
-      float2 *const st = sg;
-      // P = 1: every thread runs the same circuit, so its records are read
-      // through a wave-uniform pointer (scalar loads, matrices in SGPRs)
-      const uint64_t gp = reinterpret_cast<uint64_t>(gl);
-      const BGate *const glu = reinterpret_cast<const BGate *>(
-          (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int(gp >> 32)))) << 32) |
-          uint32_t(__builtin_amdgcn_readfirstlane(int(gp & 0xffffffffu))));
-      // P = 1: the whole workgroup runs the passes of one circuit
-      for (int g = 0; g < my_ng;) {
-        const BGate M = glu[g];  // pass record
-        const uint32_t mask = uint32_t(M.q0);
-        const int cnt = M.q1;
-        if (tid < 256) {
-          // slice bit j (j = 0..13) is the j-th lowest qubit of the mask
-          const int half = tid >> 7, v = tid & 127;
-          int32_t off = 0;
-          int j = 0;
-          for (int q = 0; q < n; ++q) {
-            if (!((mask >> q) & 1u)) continue;
-            const int jj = j - 7 * half;
-            if (jj >= 0 && jj < 7 && ((v >> jj) & 1)) off |= int32_t(1) << q;
-            ++j;
-          }
-          (half ? offhi : offlo)[v] = off;
-        }
-        __syncthreads();
-        const int nsl = 1 << (n - kSliceBits);
-        auto slice_base = [&](int si) {
-          int64_t b = 0;
-          int r = 0;
-          for (int q = 0; q < n; ++q) {
-            if ((mask >> q) & 1u) continue;
-            if ((si >> r) & 1) b |= int64_t(1) << q;
-            ++r;
-          }
-          return b;
-        };
-        int64_t base = slice_base(0);
-        for (int x = tid; x < kLdsAmps; x += kBT) lds[x] = st[base + offlo[x & 127] + offhi[x >> 7]];
-        __syncthreads();
-        for (int si = 0; si < nsl; ++si) {
-          for (int j = 1; j <= cnt;) {
-            const BGate *R = glu + g + j;
-            if (R[0].kind == SV_BATCH_GATE_LINEAR && j + 2 <= cnt && R[2].kind == SV_BATCH_GATE_GROUP &&
-                R[2].q0 == 5) {
-              apply_linear_group5(R, R + 3, lds, tid);  // its members follow the header inside the pass
-              j += 2 + 1 + 5;
-            } else {
-              j += apply_unit<kMaxGroupPass>(R, lds, kLdsAmps, tid, kBT);
-            }
-            __syncthreads();
-          }
-          // write this slice back and gather the next one in the same sweep:
-          // each thread moves only its own LDS entries, so no barrier is
-          // needed between the two, and the stores overlap the loads
-          if (si + 1 < nsl) {
-            constexpr int PER = kLdsAmps / kBT;
-            const int64_t nbase = slice_base(si + 1);
-            float2 w[PER];  // the next slice's entries of this thread, all loads in flight
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-              const int x = tid + i * kBT;
-              w[i] = st[nbase + offlo[x & 127] + offhi[x >> 7]];
-            }
-#pragma unroll
-            for (int i = 0; i < PER; ++i) {
-              const int x = tid + i * kBT;
-              st[base + offlo[x & 127] + offhi[x >> 7]] = lds[x];
-              lds[x] = w[i];
-            }
-            base = nbase;
-          } else {
-            for (int x = tid; x < kLdsAmps; x += kBT) st[base + offlo[x & 127] + offhi[x >> 7]] = lds[x];
-          }
-          __syncthreads();
-        }
-        g += 1 + cnt;
-      }
-    }
-    // <Z_0> in FP64 over this circuit's state
-    double s = 0.0;
-    for (int64_t x = lt; x < dim; x += Tc) {
-      const float2 a = in_lds ? sl[x] : sg[x];
-      const double pr = double(a.x) * double(a.x) + double(a.y) * double(a.y);
-      s += (x & 1) ? -pr : pr;
-    }
-    red[tid] = s;
-    __syncthreads();
-    for (int w = Tc / 2; w > 0; w >>= 1) {
-      if (lt < w) red[tid] += red[tid + w];
-      __syncthreads();
-    }
-    if (lt == 0) z0[I.circ[c]] = red[tid];
-    if (in_lds)
-      for (int64_t x = lt; x < dim; x += Tc) sg[x] = sl[x];
     __syncthreads();
   }
+}
+
+// <Z_0> of the slice in LDS in FP64 (qubit 0 is slice bit 0 of every pass)
+__device__ __forceinline__ void slice_share(const float2 *lds, double *red, double *out) {
+  const int tid = threadIdx.x;
+  double s = 0.0;
+#pragma unroll 8
+  for (int i = 0; i < kLdsAmps / kBT; ++i) {
+    const float2 a = lds[tid + i * kBT];
+    s += double(a.x) * double(a.x) + double(a.y) * double(a.y);
+  }
+  if (tid & 1) s = -s;
+  for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d);
+  if ((tid & 63) == 0) red[tid >> 6] = s;
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < kBT / 64; ++w) s += red[w];
+    *out = s;
+  }
+}
+
+constexpr int kPer = kLdsAmps / kBT;
+
+// One slice of a circuit's first pass, whose record is M.  It starts from
+// |0...0>, so nothing is read, and a slice without index 0 stays zero under
+// finite matrices.
+__device__ __forceinline__ void first_slice(Shared &S, UniGates M, int ngates, bool finite, int n, int si, float2 *st,
+                                            double *share) {
+  const int tid = threadIdx.x;
+  const uint32_t mask = ngates ? uint32_t(M->q0) : (1u << kSliceBits) - 1;
+  slice_tables(mask, n, S.offlo, S.offhi);
+  st += slice_base(mask, n, si);
+  const bool zero = finite && si;
+  if (!zero)
+    for (int x = tid; x < kLdsAmps; x += kBT) S.lds[x] = make_float2(x == 0 && si == 0 ? 1.f : 0.f, 0.f);
+  __syncthreads();
+  if (!zero) run_pass(M, ngates ? M->q1 : 0, S.lds);
+#pragma unroll 8
+  for (int i = 0; i < kPer; ++i) {
+    const int x = tid + i * kBT;
+    st[S.offlo[x & 127] + S.offhi[x >> 7]] = zero ? make_float2(0.f, 0.f) : S.lds[x];
+  }
+  if (!share) return;
+  if (zero) {
+    if (tid == 0) *share = 0.0;
+  } else {
+    slice_share(S.lds, S.red, share);
+  }
+}
+
+// Entry and slice of the t-th slice of a level.
+struct LevelArg {
+  const BEntry *entries;
+  int count[kBigSizes];
+};
+__device__ __forceinline__ bool find_slice(const LevelArg &L, int t, BEntry *e, int *si) {
+  int at = 0;
+#pragma unroll
+  for (int g = 0; g < kBigSizes; ++g) {
+    const int bits = kBigSizes - g, total = L.count[g] << bits;
+    if (t < total) {
+      *e = L.entries[at + (t >> bits)];
+      *si = t & ((1 << bits) - 1);
+      return true;
+    }
+    t -= total;
+    at += L.count[g];
+  }
+  return false;
+}
+
+// The units of a circuit held in LDS, in lockstep over its pack: one unit
+// (gate, group or linear record) per step, and a circuit past its last one
+// only meets the barriers.
+template <typename GP>
+__device__ __forceinline__ void run_pack(GP gl, int my_ng, int ngates, bool linear, float2 *sl, int dim, int lt,
+                                         int Tc) {
+  int r = 0;  // this circuit's next record
+  for (int g = 0; g < ngates; ++g) {
+    if (linear) {
+      float2 v[32];
+      const bool lin = g < my_ng && gl[r].kind == SV_BATCH_GATE_LINEAR;
+      if (lin)
+        gather_linear(gl + r, sl, dim, lt, Tc, v);
+      else if (g < my_ng)
+        r += apply_unit<kMaxGroupLds>(gl + r, sl, dim, lt, Tc);
+      __syncthreads();
+      if (lin) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i)
+          if (lt + Tc * i < dim) sl[lt + Tc * i] = v[i];
+        r += 2;
+      }
+    } else if (g < my_ng) {
+      r += apply_unit<kMaxGroupLds>(gl + r, sl, dim, lt, Tc);
+    }
+    __syncthreads();
+  }
+}
+
+// Workgroups [0, nitems): a pack of circuits whose states fit LDS, from
+// |0...0> to the write-back, or the slice with index 0 of a larger circuit's
+// first pass.  The rest: the other slices of those first passes.
+__global__ __launch_bounds__(kBT) void k_batch(const BItem *__restrict__ items, int nitems,
+                                               const BGate *__restrict__ gates, float2 *__restrict__ states,
+                                               double *__restrict__ z0, double *__restrict__ part, LevelArg level) {
+  __shared__ Shared S;
+  const int tid = threadIdx.x;
+  int it = blockIdx.x, si = 0;
+  if (it >= nitems) {
+    BEntry e;
+    if (!find_slice(level, it - nitems, &e, &si) || si == 0) return;
+    it = e.item;
+  }
+  const BItem &I = items[it];
+  const int n = I.n;
+  if (n > kSliceBits) {
+    const UniGates M = uniform(gates + I.gate_off[0]);
+    const bool only = I.ngc[0] == 0 || 1 + M->q1 == I.ngc[0];
+    first_slice(S, M, I.ngc[0], I.flags & kItemFinite, n, si, states + I.state_off[0],
+                only ? part + I.share + si : nullptr);
+    return;
+  }
+  const int P = I.P, ngates = I.ngates;
+  const int Tc = kBT / P;
+  const int c = tid / Tc, lt = tid % Tc;
+  const int dim = 1 << n;
+  float2 *const sl = S.lds + c * dim;
+  float2 *const sg = states + I.state_off[c];
+  const BGate *gl = gates + I.gate_off[c];
+  const int my_ng = I.ngc[c];
+  for (int x = lt; x < dim; x += Tc) sl[x] = make_float2(x == 0 ? 1.f : 0.f, 0.f);
+  __syncthreads();
+  // a circuit's records through a wave-uniform pointer (scalar loads, the
+  // matrices in SGPRs) where a wave holds one circuit
+  if (Tc >= 64)
+    run_pack(uniform(gl), __builtin_amdgcn_readfirstlane(my_ng), ngates, I.flags & kItemLinear, sl, dim, lt, Tc);
+  else
+    run_pack((LaneGates)gl, my_ng, ngates, I.flags & kItemLinear, sl, dim, lt, Tc);
+  // <Z_0> in FP64
+  double s = 0.0;
+  for (int x = lt; x < dim; x += Tc) {
+    const float2 a = sl[x];
+    const double pr = double(a.x) * double(a.x) + double(a.y) * double(a.y);
+    s += (x & 1) ? -pr : pr;
+    sg[x] = a;
+  }
+  S.red[tid] = s;
+  __syncthreads();
+  for (int w = Tc / 2; w > 0; w >>= 1) {
+    if (lt < w) S.red[tid] += S.red[tid + w];
+    __syncthreads();
+  }
+  if (lt == 0) z0[I.circ[c]] = S.red[tid];
+}
+
+// A later pass of the circuits that have one.  Workgroups stride over the
+// level's slices; a slice is in registers by the time the one before it is
+// done (a lone workgroup fills the CU, so nothing else covers the loads).
+// Passes of many gates are bound by the vector units (1798 slices: 0.52 ms,
+// 0.29 of it multiply-adds), short ones by memory (940 slices: 76 us, 3.2 TB/s;
+// 148 us with a workgroup per slice).
+__global__ __launch_bounds__(kBT) void k_batch_level(const BItem *__restrict__ items, const BGate *__restrict__ gates,
+                                                     float2 *__restrict__ states, double *__restrict__ part, LevelArg level,
+                                                     int total) {
+  __shared__ float2 lds[kLdsAmps];
+  // three sets: a slice's stores, the next one's loads, and the set that a late
+  // thread of the slice before may still read
+  __shared__ int32_t offlo[3][128], offhi[3][128];
+  __shared__ double red[kBT / 64];
+  const int tid = threadIdx.x;
+  struct Slice {
+    UniGates M;
+    float2 *st;
+    double *share;  // null unless this is the circuit's last pass
+  };
+  auto open = [&](int t, int buf) __attribute__((always_inline)) {
+    // siblings, which share cache lines, on one XCD: workgroups go round the eight
+    const int u = t < (total & ~15) ? (t & ~15) | (t & 7) << 1 | (t >> 3 & 1) : t;
+    BEntry e = {0, 0};
+    int si = 0;
+    find_slice(level, u, &e, &si);
+    const BItem &I = items[e.item];
+    Slice s;
+    s.M = uniform(gates + I.gate_off[0] + e.rec);
+    const uint32_t mask = uint32_t(s.M->q0);
+    s.st = states + I.state_off[0] + slice_base(mask, I.n, si);
+    s.share = e.rec + 1 + s.M->q1 == I.ngc[0] ? part + I.share + si : nullptr;
+    slice_tables(mask, I.n, offlo[buf], offhi[buf]);
+    return s;
+  };
+  float2 w[kPer];
+  int t = blockIdx.x, buf = 0;
+  Slice cur = open(t, 0);
+  __syncthreads();
+  auto entry = [&](const Slice &s, int b, int i) __attribute__((always_inline)) -> float2 & {
+    return s.st[offlo[b][tid & 127] + offhi[b][(tid >> 7) + i * (kBT >> 7)]];
+  };
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) w[i] = entry(cur, 0, i);
+  for (;;) {
+    // each thread's own entries, which it stored a moment ago
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) lds[tid + i * kBT] = w[i];
+    const int next = t + gridDim.x;
+    const bool more = next < total;
+    const int nbuf = buf == 2 ? 0 : buf + 1;
+    Slice nx = cur;
+    if (more) nx = open(next, nbuf);
+    __syncthreads();
+    if (more) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) w[i] = entry(nx, nbuf, i);
+    }
+    run_pass(cur.M, cur.M->q1, lds);
+#pragma unroll 8
+    for (int i = 0; i < kPer; ++i) entry(cur, buf, i) = lds[tid + i * kBT];
+    if (cur.share) slice_share(lds, red, cur.share);
+    if (!more) break;
+    cur = nx;
+    t = next;
+    buf = nbuf;
+  }
+}
+
+// <Z_0> of the circuits that ran in passes: the sum of its slices' shares.
+__global__ __launch_bounds__(64) void k_batch_z0(const BItem *__restrict__ items, const BEntry *__restrict__ entries,
+                                                 const double *__restrict__ part, double *__restrict__ z0, int count) {
+  const int t = blockIdx.x * 64 + threadIdx.x;
+  if (t >= count) return;
+  const BItem &I = items[entries[t].item];
+  double s = 0.0;
+  for (int j = 0; j < 1 << (I.n - kSliceBits); ++j) s += part[I.share + j];
+  z0[I.circ[0]] = s;
 }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // Device side of a packed batch: where its records sit in the workspace.
 struct DevBatch {
-  unsigned *counter = nullptr;
   double *z0 = nullptr;
   BItem *items = nullptr;
   BGate *gates = nullptr;
+  BEntry *entries = nullptr;
+  double *part = nullptr;  // shares of <Z_0>
+  std::vector<BLevel> levels;
   int nitems = 0, ncirc = 0;
 };
 
 // Copy a packed batch's records into the workspace (asynchronous on st).
 int upload_packed(const Packed &pk, void *ws_dev, size_t ws_bytes, hipStream_t st, DevBatch *d) {
-  const size_t o_cnt = 0;
-  const size_t o_z0 = 256;
+  const size_t o_z0 = 0;
   const size_t o_items = o_z0 + align256(sizeof(double) * size_t(std::max(1, pk.ncirc)));
   const size_t o_gates = o_items + align256(sizeof(BItem) * std::max<size_t>(1, pk.items.size()));
-  const size_t need = o_gates + align256(sizeof(BGate) * std::max<size_t>(1, pk.gates.size()));
+  const size_t o_entries = o_gates + align256(sizeof(BGate) * std::max<size_t>(1, pk.gates.size()));
+  const size_t o_part = o_entries + align256(sizeof(BEntry) * std::max<size_t>(1, pk.entries.size()));
+  size_t shares = 0;
+  if (!pk.levels.empty())
+    for (int g = 0; g < kBigSizes; ++g) shares += size_t(pk.levels[0].count[g]) << (kBigSizes - g);
+  const size_t need = o_part + align256(sizeof(double) * shares);
   if (!ws_dev || ws_bytes < need) {
     set_error("batch workspace too small");
     return SV_ERR_ARG;
   }
   char *ws = static_cast<char *>(ws_dev);
-  d->counter = reinterpret_cast<unsigned *>(ws + o_cnt);
   d->z0 = reinterpret_cast<double *>(ws + o_z0);
   d->items = reinterpret_cast<BItem *>(ws + o_items);
   d->gates = reinterpret_cast<BGate *>(ws + o_gates);
+  d->entries = reinterpret_cast<BEntry *>(ws + o_entries);
+  d->part = reinterpret_cast<double *>(ws + o_part);
+  d->levels = pk.levels;
   d->nitems = int(pk.items.size());
   d->ncirc = pk.ncirc;
   if (!pk.items.empty())
     SV_HIP_CHECK(hipMemcpyAsync(d->items, pk.items.data(), sizeof(BItem) * pk.items.size(), hipMemcpyHostToDevice, st));
   if (!pk.gates.empty())
     SV_HIP_CHECK(hipMemcpyAsync(d->gates, pk.gates.data(), sizeof(BGate) * pk.gates.size(), hipMemcpyHostToDevice, st));
+  if (!pk.entries.empty())
+    SV_HIP_CHECK(hipMemcpyAsync(d->entries, pk.entries.data(), sizeof(BEntry) * pk.entries.size(),
+                                hipMemcpyHostToDevice, st));
   return SV_OK;
 }
 
-// One persistent launch over an uploaded batch; z0_host (optional) receives
+// The launches of an uploaded batch; z0_host (optional) receives
 // <Z_0> per circuit and makes the call synchronous; ms_out (optional) times the kernel.
 int launch_packed(const DevBatch &d, void *states_dev, double *z0_host, hipStream_t st, float *ms_out) {
   int dev = 0, cus = 256;
@@ -469,13 +666,38 @@ int launch_packed(const DevBatch &d, void *states_dev, double *z0_host, hipStrea
     SV_HIP_CHECK(hipEventCreate(&e0));
     SV_HIP_CHECK(hipEventCreate(&e1));
   }
-  hipLaunchKernelGGL(k_batch_reset, dim3(1), dim3(64), 0, st, d.counter);
-  SV_HIP_CHECK(hipGetLastError());
   if (ms_out) SV_HIP_CHECK(hipEventRecord(e0, st));
-  const int grid = std::max(1, std::min<int>(cus, d.nitems));
-  hipLaunchKernelGGL(k_batch, dim3(grid), dim3(kBT), 0, st, d.items, d.nitems, d.gates,
-                     static_cast<float2 *>(states_dev), d.z0, d.counter);
-  SV_HIP_CHECK(hipGetLastError());
+  auto level = [&](size_t l, int *slices) {
+    LevelArg a;
+    std::memset(&a, 0, sizeof(a));
+    *slices = 0;
+    if (l >= d.levels.size()) return a;
+    a.entries = d.entries + d.levels[l].first;
+    for (int g = 0; g < kBigSizes; ++g) {
+      a.count[g] = d.levels[l].count[g];
+      *slices += a.count[g] << (kBigSizes - g);
+    }
+    return a;
+  };
+  float2 *const states = static_cast<float2 *>(states_dev);
+  int slices = 0, shares = 0, big = 0;
+  const LevelArg l0 = level(0, &shares);
+  for (int g = 0; g < kBigSizes; ++g) big += l0.count[g];
+  if (d.nitems > 0) {
+    hipLaunchKernelGGL(k_batch, dim3(unsigned(d.nitems + shares)), dim3(kBT), 0, st, d.items, d.nitems, d.gates, states,
+                       d.z0, d.part, l0);
+    SV_HIP_CHECK(hipGetLastError());
+  }
+  for (size_t l = 1; l < d.levels.size(); ++l) {
+    const LevelArg a = level(l, &slices);
+    hipLaunchKernelGGL(k_batch_level, dim3(unsigned(std::min(cus, slices))), dim3(kBT), 0, st, d.items, d.gates, states,
+                       d.part, a, slices);
+    SV_HIP_CHECK(hipGetLastError());
+  }
+  if (big) {
+    hipLaunchKernelGGL(k_batch_z0, dim3(unsigned((big + 63) / 64)), dim3(64), 0, st, d.items, l0.entries, d.part, d.z0, big);
+    SV_HIP_CHECK(hipGetLastError());
+  }
   if (ms_out) SV_HIP_CHECK(hipEventRecord(e1, st));
   if (z0_host && d.ncirc > 0)
     SV_HIP_CHECK(hipMemcpyAsync(z0_host, d.z0, sizeof(double) * size_t(d.ncirc), hipMemcpyDeviceToHost, st));
@@ -524,7 +746,7 @@ int sv_batch_run(int count, const sv_batch_circuit *circs, void *states_dev, siz
       default_config(cfg);
     }
     Packed pk;
-    int rc = pack_batch(count, circs, states_bytes, state_offsets, cfg, &pk);
+    int rc = pack_batch(count, circs, states_bytes, state_offsets, cfg, &pk, true);
     if (rc) return rc;
     return run_packed(pk, states_dev, z0_host, ws_dev, ws_bytes, static_cast<hipStream_t>(stream), nullptr);
   });
@@ -557,7 +779,7 @@ int sv_batch_autotune(int count, const sv_batch_circuit *circs, void *states_dev
     std::vector<double> z(std::max<size_t>(1, sample.size()));
     auto measure = [&](const int32_t *c, double *t_out) -> int {
       Packed pk;
-      int rc = pack_batch(int(sample.size()), sample.data(), states_bytes, offs.data(), c, &pk);
+      int rc = pack_batch(int(sample.size()), sample.data(), states_bytes, offs.data(), c, &pk, true);
       if (rc) return rc;
       float ms = 0.f;
       rc = run_packed(pk, states_dev, z.data(), ws_dev, ws_bytes, st, &ms);  // warm-up
@@ -620,7 +842,7 @@ extern "C" int sv_batch_prepare(int count, const sv_batch_circuit *circs, size_t
       default_config(cfg);
     }
     Packed pk;
-    int rc = pack_batch(count, circs, states_bytes, state_offsets, cfg, &pk);
+    int rc = pack_batch(count, circs, states_bytes, state_offsets, cfg, &pk, true);
     if (rc) return rc;
     sv_batch_prepared *p = new sv_batch_prepared();
     hipStream_t st = static_cast<hipStream_t>(stream);

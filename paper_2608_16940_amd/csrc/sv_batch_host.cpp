@@ -1,4 +1,4 @@
-// Batched path, host pass: per-circuit records for the persistent kernel
+// Batched path, host pass: per-circuit records for the batched kernels
 // (see sv_batch_host.h).  Plain C++, no HIP: also built on its own for the
 // host sanitizer checks.
 #include "sv_batch_host.h"
@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
+#include <cmath>
 #include <cstring>
 #include <map>
 #include <new>
@@ -187,10 +188,12 @@ std::vector<BGate> group_single_qubit(const std::vector<BGate> &g, bool passes) 
   return out;
 }
 
-// Units (a gate, or a group with its members) in a record list without passes.
+// Units (a gate, a group with its members, a linear record and its masks) in
+// a record list without passes.
 int count_units(const std::vector<BGate> &g) {
   int u = 0;
-  for (size_t i = 0; i < g.size(); i += (g[i].kind == SV_BATCH_GATE_GROUP) ? 1 + size_t(g[i].q0) : 1) ++u;
+  for (size_t i = 0; i < g.size(); ++u)
+    i += g[i].kind == SV_BATCH_GATE_GROUP ? 1 + size_t(g[i].q0) : (g[i].kind == SV_BATCH_GATE_LINEAR ? 2 : 1);
   return u;
 }
 
@@ -218,7 +221,8 @@ void default_config(int32_t *cfg) {
 // Validate circuit i, fuse adjacent single-qubit gates on the same qubit
 // (FP64, later gate on the left), cut it into passes if its state exceeds a
 // slice, group single-qubit runs.  Touches only circuit i's inputs and g.
-int prepare_circuit(const sv_batch_circuit &C, int64_t state_offset, size_t states_bytes, std::vector<BGate> &g) {
+int prepare_circuit(const sv_batch_circuit &C, int64_t state_offset, size_t states_bytes, std::vector<BGate> &g,
+                    bool merge) {
   if (C.n_qubits < 1 || C.n_qubits > SV_BATCH_MAX_QUBITS || C.n_gates < 0 ||
       (C.n_gates > 0 && (!C.kinds || !C.qubits)) || state_offset < 0 || (state_offset & 7) ||
       uint64_t(state_offset) + (uint64_t(8) << C.n_qubits) > uint64_t(states_bytes))
@@ -277,7 +281,10 @@ int prepare_circuit(const sv_batch_circuit &C, int64_t state_offset, size_t stat
     }
   }
   flush();
-  if (C.n_qubits > kSliceBits) g = make_passes(g, C.n_qubits);
+  if (C.n_qubits > kSliceBits)
+    g = make_passes(g, C.n_qubits);
+  else if (merge)
+    g = merge_cnots(g, 0, g.size());
   g = group_single_qubit(g, C.n_qubits > kSliceBits);
   return CIRC_OK;
 }
@@ -288,14 +295,14 @@ int prepare_circuit(const sv_batch_circuit &C, int64_t state_offset, size_t stat
 // gate count so that packs hold circuits of similar length, cut packs, order
 // by cost.
 int pack_batch(int count, const sv_batch_circuit *circs, size_t states_bytes, const int64_t *state_offsets,
-               const int32_t *cfg, Packed *out) {
+               const int32_t *cfg, Packed *out, bool merge) {
   std::vector<std::vector<BGate>> fused(static_cast<size_t>(count));
   std::vector<int> status(static_cast<size_t>(count), CIRC_OK);
   std::atomic<int> next{0};
   auto work = [&]() {
     for (int i; (i = next.fetch_add(1)) < count;) {
       try {
-        status[size_t(i)] = prepare_circuit(circs[i], state_offsets[i], states_bytes, fused[size_t(i)]);
+        status[size_t(i)] = prepare_circuit(circs[i], state_offsets[i], states_bytes, fused[size_t(i)], merge);
       } catch (const std::bad_alloc &) {
         status[size_t(i)] = CIRC_NOMEM;
       }
@@ -345,6 +352,7 @@ int pack_batch(int count, const sv_batch_circuit *circs, size_t states_bytes, co
       it.n = n;
       it.P = P;
       int ng = 0;
+      it.flags = kItemFinite;
       for (int c = 0; c < P; ++c) {
         const int id = ids[pos + size_t(c)];
         it.circ[c] = id;
@@ -353,16 +361,58 @@ int pack_batch(int count, const sv_batch_circuit *circs, size_t states_bytes, co
         ng = std::max(ng, it.ngc[c]);
         it.gate_off[c] = gate_off[size_t(id)];
         it.state_off[c] = state_offsets[id] / 8;
+        for (const BGate &b : fused[size_t(id)]) {
+          if (b.kind == SV_BATCH_GATE_LINEAR && n <= kSliceBits) it.flags |= kItemLinear;
+          if (b.kind == SV_BATCH_GATE_1Q)
+            for (float v : b.m)
+              if (!std::isfinite(v)) it.flags &= ~kItemFinite;
+        }
       }
       it.ngates = ng;
       pos += size_t(P);
-      const double cost = double(ng + 1) * double(int64_t(1) << n) * double(P);
+      // time of its part of the first launch: a pack's units, at four gates
+      // each, or the gates of a first pass
+      double cost = double(ng) * double(int64_t(1) << n) * double(P) / kLdsAmps;
+      if (n > kSliceBits) cost = ng ? fused[size_t(it.circ[0])][0].q1 / 4.0 : 0.0;
       items.push_back({cost, it});
     }
   }
   std::stable_sort(items.begin(), items.end(),
                    [](const std::pair<double, BItem> &a, const std::pair<double, BItem> &b) { return a.first > b.first; });
   for (auto &pr : items) out->items.push_back(pr.second);
+  // the launches of the circuits that run in passes
+  struct At {
+    BEntry e;
+    int n, len;
+  };
+  std::vector<std::vector<At>> levels;
+  int32_t shares = 0;
+  for (size_t i = 0; i < out->items.size(); ++i) {
+    BItem &it = out->items[i];
+    if (it.n <= kSliceBits) continue;
+    it.share = shares;
+    shares += 1 << (it.n - kSliceBits);
+    if (levels.empty()) levels.emplace_back();
+    if (it.ngc[0] == 0) levels[0].push_back({{int32_t(i), 0}, it.n, 0});
+    size_t lv = 0;
+    for (int32_t r = 0; r < it.ngc[0]; ++lv) {
+      if (levels.size() <= lv) levels.emplace_back();
+      const int32_t len = out->gates[size_t(it.gate_off[0]) + size_t(r)].q1;
+      levels[lv].push_back({{int32_t(i), r}, it.n, len});
+      r += 1 + len;
+    }
+  }
+  for (auto &v : levels) {
+    std::stable_sort(v.begin(), v.end(), [](const At &a, const At &b) { return a.n != b.n ? a.n > b.n : a.len > b.len; });
+    BLevel L;
+    std::memset(&L, 0, sizeof(L));
+    L.first = int32_t(out->entries.size());
+    for (const At &a : v) {
+      out->entries.push_back(a.e);
+      ++L.count[SV_BATCH_MAX_QUBITS - a.n];
+    }
+    out->levels.push_back(L);
+  }
   return SV_OK;
 }
 
@@ -377,9 +427,16 @@ extern "C" {
 size_t sv_batch_workspace_bytes(int count, const sv_batch_circuit *circs) {
   if (count < 0 || (count > 0 && !circs)) return 0;
   size_t ng = 0;  // at most one pass record and half a group record per gate on top of the gates
-  for (int i = 0; i < count; ++i) ng += 3 * size_t(std::max(0, circs[i].n_gates));
+  size_t shares = 0;  // of <Z_0>, one per 2^14 amplitudes
+  for (int i = 0; i < count; ++i) {
+    ng += 3 * size_t(std::max(0, circs[i].n_gates));
+    if (circs[i].n_qubits > kSliceBits && circs[i].n_qubits <= SV_BATCH_MAX_QUBITS)
+      shares += size_t(1) << (circs[i].n_qubits - kSliceBits);
+  }
+  // and an entry per pass (a pass holds a gate) and per circuit
   return 256 + align256_(sizeof(double) * size_t(std::max(1, count))) +
-         align256_(sizeof(BItem) * size_t(std::max(1, count))) + align256_(sizeof(BGate) * std::max<size_t>(1, ng));
+         align256_(sizeof(BItem) * size_t(std::max(1, count))) + align256_(sizeof(BGate) * std::max<size_t>(1, ng)) +
+         align256_(sizeof(BEntry) * (ng + size_t(std::max(1, count)))) + align256_(sizeof(double) * shares);
 }
 
 }  // extern "C"
