@@ -15,8 +15,8 @@
  * circuit.  Larger states live in the caller's state buffer and run as
  * passes: each pass streams every 2^14-amplitude slice of a chosen set of 14
  * qubits through LDS and applies there every gate that acts only on them.
- * Workgroups take packs from an atomic queue ordered by decreasing cost and
- * exit when the queue is empty.
+ * The first launch holds all packs, longest first, and the first passes; the
+ * p-th passes of all circuits that have one are a launch of their own.
  */
 #ifndef SV_BATCH_H_
 #define SV_BATCH_H_

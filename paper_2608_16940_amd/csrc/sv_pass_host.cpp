@@ -14,15 +14,24 @@ namespace {
 inline int popc(uint64_t x) { return __builtin_popcountll(x); }
 
 // Tile bits of a pass on n qubits, and the lowest bits every tile holds.
-// States that stay in the caches (2^21 amplitudes, 16 MiB) run 2^12 tiles so
-// that more workgroups share the state, and take runs of four amplitudes;
-// larger ones take the widest tile and runs of 16 (128 bytes, a cache line).
+// Wider tiles take more gates per pass, narrower ones spread a small state over
+// more CUs; runs of 8 amplitudes do while the state stays in the caches, of a
+// cache line (16) beyond.  Twelve brickwork layers in blocks of five / six
+// qubits, us, by tile bits:
+//   n=14  12: 140/211  13: 180/261  14: 249/366
+//   n=16  12: 146/256  13: 185/301  14: 307/446
+//   n=20  12: 273/335  13: 261/389  14: 403/544
+//   n=21  12: 400/463  13: 352/398  14: 462/554
+//   n=22  12: 768/995  13: 712/1015 14: 632/859
+//   n=24  12: 2571/3447 13: 2487/3336 14: 2333/2940
+// and one workgroup for all of n=12 (99/166) against 2^11 tiles (134/188).
 struct Shape {
   int S, low;
 };
 Shape shape_for(int n) {
-  if (n <= kMaxS) return {n, n};
-  if (n <= 21) return {12, 2};
+  if (n <= 12) return {n, n};
+  if (n <= 20) return {12, 3};
+  if (n == 21) return {13, 3};
   return {14, 4};
 }
 
