@@ -16,7 +16,7 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 SOURCES = ["sv_api.hip", "sv_kernels.hip", "sv_tile.hip", "sv_plan.cpp", "sv_batch.hip", "sv_mlp.hip", "sv_density.hip", "sv_batch_host.cpp",
            "sv_mlp_host.cpp", "sv_host.cpp", "sv_noalloc.hip", "sv_pass.hip",
-           "sv_pass_host.cpp", "sv_prog.hip", "sv_prog_host.cpp"]
+           "sv_pass_host.cpp", "sv_prog.hip", "sv_prog_host.cpp", "sv_chain.hip"]
 
 FLAGS = [
     "--offload-arch=gfx950",

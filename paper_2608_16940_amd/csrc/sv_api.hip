@@ -14,6 +14,7 @@
 #include "sv_diagcover.h"
 #include "sv_permute_host.h"
 #include "sv_internal.h"
+#include "sv_chain.h"
 #include "sv_pass.h"
 #include "sv_prog.h"
 #include "sv_plan.h"
@@ -564,6 +565,98 @@ int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
     rc = release_slot(s, slot);
     if (rc) return rc;
     i = j;
+  }
+  s->stats = before;
+  q.add.launches = launches;
+  add_stats(&s->stats, q.add);
+  finish_sequence(s, q, gates);
+  return SV_OK;
+}
+
+// Density handles: a plan's gates keep the arithmetic of their own sweeps bit
+// for bit, so they share passes as chains (sv_chain_host.h).
+bool chainable(const sv_state *s) {
+  return s->dm_n != 0 && s->variant == SV_VARIANT_AUTO && !s->lazy && s->mfma_min_k == 4 &&
+         s->opsrc == SV_MFMA_OPERAND_AUTO && s->tile_order == -1 && s->prec == SV_PREC_FP32;
+}
+
+// Runs valid gates in order as chains and single sweeps.  The operands of
+// steps that follow each other are staged together.
+int run_chains(sv_state *s, const std::vector<SeqGate> &gates) {
+  Sequence q;
+  std::memset(&q.add, 0, sizeof(q.add));
+  std::memcpy(q.Lend, s->L, sizeof(q.Lend));
+  pass::Item it;
+  for (const SeqGate &g : gates)
+    if (resolve_gate(s->n, g, q.Lend, &q.add, &it)) q.items.push_back(it);
+  std::vector<chain::Step> steps = chain::build(s->n, q.items);
+  const sv_stats before = s->stats;
+  int64_t launches = 0;
+  std::vector<char> ops;
+  std::vector<Lowered> single;
+  std::vector<size_t> off;
+  constexpr size_t kStepsAtOnce = 64;
+  for (size_t i = 0; i < steps.size();) {
+    // operands of steps [i, j), as many as a staging slot takes
+    ops.clear();
+    single.clear();
+    off.clear();
+    const size_t i0 = i;
+    size_t j = i;
+    for (; j < steps.size() && j - i0 < kStepsAtOnce; ++j) {
+      chain::Step &x = steps[j];
+      size_t bytes = 0;
+      single.emplace_back();
+      Lowered &one = single.back();
+      if (!x.fused) {
+        const pass::Item &g = q.items[size_t(x.items[0])];
+        const int rc = lower(s, g.m, g.A, g.k, false, &one);
+        if (rc) return rc;
+        bytes = align256(one.op.size());
+      } else {
+        for (int g : x.items) bytes += align256(mfma_operand_bytes(q.items[size_t(g)].k, s->prec));
+      }
+      if (j > i && ops.size() + bytes > kRingSlotBytes) break;
+      off.push_back(ops.size());
+      ops.resize(off.back() + bytes);
+      if (!x.fused) {
+        if (bytes) std::memcpy(ops.data() + off.back(), one.op.data(), one.op.size());
+        continue;
+      }
+      size_t at = 0;
+      for (size_t g = 0; g < x.items.size(); ++g) {
+        const pass::Item &y = q.items[size_t(x.items[g])];
+        pack_mfma_operand(y.k, s->prec, y.m, ops.data() + off.back() + at);
+        x.gate[g].op = int32_t(at);
+        at += align256(mfma_operand_bytes(y.k, s->prec));
+      }
+    }
+    void *dev = nullptr;
+    int slot = -1;
+    if (!ops.empty()) {
+      const int rc = stage(s, ops.data(), ops.size(), &dev, &slot);
+      if (rc) return rc;
+    }
+    for (; i < j; ++i) {
+      const char *data = static_cast<const char *>(dev) + off[i - i0];
+      if (!steps[i].fused) {
+        const int64_t l0 = s->stats.launches;
+        const int rc = launch_lowered(s, single[i - i0], data);
+        if (rc) return rc;
+        launches += s->stats.launches - l0;
+        continue;
+      }
+      const hipError_t e = chain::launch(s->n, steps[i], s->amps, data, s->st);
+      if (e != hipSuccess) {
+        set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
+        return SV_ERR_DEVICE;
+      }
+      ++launches;
+    }
+    if (slot >= 0) {
+      const int rc = release_slot(s, slot);
+      if (rc) return rc;
+    }
   }
   s->stats = before;
   q.add.launches = launches;
@@ -1281,7 +1374,7 @@ int sv_run_plan(sv_state *s, const sv_plan *p) {
     const size_t nb = p->blocks.size(), nq = size_t(std::max(p->n, s->n));
     std::vector<int64_t> next(nq, INT64_MAX);
     std::vector<std::vector<int64_t>> hints(nb);
-    const bool fuse = fusible(s);
+    const bool chains = chainable(s), fuse = fusible(s) || chains;
     for (size_t i = nb; i-- > 0;) {
       // a fused run leaves the hints of its last block
       if (!fuse || i + 1 == nb || p->blocks[i + 1].swap) hints[i] = next;
@@ -1324,7 +1417,7 @@ int sv_run_plan(sv_state *s, const sv_plan *p) {
           rc = sv_hint_next_use(s, hints[j - 1].data());
           if (rc) return rc;
         }
-        rc = run_gates(s, gates);
+        rc = chains ? run_chains(s, gates) : run_gates(s, gates);
         if (rc) return rc;
         i = j;
         continue;

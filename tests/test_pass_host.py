@@ -64,3 +64,20 @@ def test_programs_equal_gates_one_by_one():
     r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-6000:])
     assert "program checks passed" in r.stdout
+
+
+def test_chains_equal_gates_one_by_one():
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    out = os.path.join(ROOT, "_build")
+    os.makedirs(out, exist_ok=True)
+    exe = os.path.join(out, "chain_check")
+    r = subprocess.run([gxx, "-std=c++17", "-O2", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                        "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                        os.path.join(ROOT, "tests", "native", "chain_check.cpp"), "-o", exe],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, (r.stdout[-2000:], r.stderr[-6000:])
+    assert "chain checks passed" in r.stdout
