@@ -525,8 +525,15 @@ int launch_pass(sv_state *s, const pass::Fused &f, const char *dev) {
   return SV_OK;
 }
 
-// Runs valid gates in order through fused passes.
+int run_list(sv_state *s, const std::vector<SeqGate> &gates);
+
+// Runs valid gates in order through fused passes.  Sequences of narrow gates
+// alone (an unfused circuit as a plan) run as programs: a one-qubit gate in a
+// pass of matrix-core gates acts as a five-qubit one.
 int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
+  bool narrow = s->n >= prog::kMinQubits;
+  for (const SeqGate &g : gates) narrow = narrow && (g.k == 1 || (g.k == 2 && is_diagonal(g.m, 2)));
+  if (narrow) return run_list(s, gates);
   Sequence q;
   plan_sequence(s, gates, s->L, &q);
   const sv_stats before = s->stats;

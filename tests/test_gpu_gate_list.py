@@ -65,3 +65,23 @@ def test_what_precedes_a_bad_gate_is_applied():
     a.sync(), b.sync()
     assert (a.copy_out() == b.copy_out()).all()
     assert a.stats()["gate_sweeps"] == b.stats()["gate_sweeps"]
+
+
+@pytest.mark.parametrize("n", [3, 4, 12, 20])
+def test_unfused_plan_equals_the_list(n):
+    import torch
+    from paper_2608_16940_amd import Plan, StateVector
+    gates = C.brickwork(n, 10, 7)
+    plan = Plan.greedy(n, gates, 1)
+    a, b = StateVector(n), StateVector(n)
+    g = torch.Generator(device="cuda:0").manual_seed(n)
+    torch.view_as_real(a.amps).normal_(0.0, 2.0 ** (-(n + 1) / 2), generator=g)
+    b.amps.copy_(a.amps)
+    plan.run(a)
+    for x in plan.blocks():
+        b.apply(x["matrix"], x["targets"])
+    sa, sb = a.stats(), b.stats()
+    sa.pop("launches"), sb.pop("launches")
+    assert sa == sb
+    d = (a.amps - b.amps).to(torch.complex128).norm() / b.amps.to(torch.complex128).norm()
+    assert float(d) <= 8 * 2.0 ** -24 * sum(1 << len(x.targets) for x in gates)
