@@ -34,14 +34,17 @@ def _stream_ptr(stream):
     return ctypes.c_void_p(int(stream.cuda_stream)), stream
 
 
+_LIST_CHUNK = 1024  # gates per call: bounds the copy of their matrices (64 MiB at six qubits)
+
+
 def _gate_list(gates):
     """Arguments of sv_apply_gates, or None for a list that is not one complex matrix of
-    2^k x 2^k and k integers per gate (applied one by one, so that what precedes a bad gate acts)."""
+    2^k x 2^k and k <= 6 integers per gate (applied one by one, so that what precedes a bad gate acts)."""
     try:
         targets = [g.targets for g in gates]
         ks = [len(t) for t in targets]
         matrices = [np.ascontiguousarray(g.matrix, np.complex128) for g in gates]
-        if [m.size for m in matrices] != [1 << (2 * k) for k in ks]:
+        if max(ks) > 6 or [m.size for m in matrices] != [1 << (2 * k) for k in ks]:
             return None
         ks = array.array("i", ks)
         flat = array.array("i", itertools.chain.from_iterable(targets))
@@ -100,13 +103,18 @@ class StateVector:
 
     def apply_gates(self, gates):
         """The gates (objects with ``matrix`` and ``targets``) in order, as ``apply`` one by one."""
-        if isinstance(gates, (list, tuple)) and type(self).apply is StateVector.apply:
-            call = _gate_list(gates)
+        if not isinstance(gates, (list, tuple)) or type(self).apply is not StateVector.apply:
+            for g in gates:
+                self.apply(g.matrix, g.targets)
+            return
+        for i in range(0, len(gates), _LIST_CHUNK):
+            part = gates[i:i + _LIST_CHUNK]
+            call = _gate_list(part)
             if call is not None:
                 check(lib().sv_apply_gates(self._h, *call))
-                return
-        for g in gates:
-            self.apply(g.matrix, g.targets)
+                continue
+            for g in part:
+                self.apply(g.matrix, g.targets)
 
     def permute_layout(self, layout):
         L = np.ascontiguousarray(np.asarray(layout, dtype=np.int32))

@@ -85,3 +85,19 @@ def test_unfused_plan_equals_the_list(n):
     assert sa == sb
     d = (a.amps - b.amps).to(torch.complex128).norm() / b.amps.to(torch.complex128).norm()
     assert float(d) <= 8 * 2.0 ** -24 * sum(1 << len(x.targets) for x in gates)
+
+
+def test_long_and_odd_lists():
+    from paper_2608_16940_amd import StateVector
+    n = 12
+    gates = C.brickwork(n, 100, 9)  # more than one call's gates
+    seven = np.linalg.qr(np.random.default_rng(1).standard_normal((128, 128)))[0].astype(complex)
+    gates = gates[:700] + [C.Gate("wide", tuple(range(7)), seven)] + gates[700:]
+    a, b = StateVector(n), StateVector(n)
+    a.reset(), b.reset()
+    a.apply_gates([])
+    a.apply_gates(gates)
+    b.apply_gates(iter(gates))  # not a list: one by one
+    assert a.stats()["by_variant"] == b.stats()["by_variant"]
+    x, y = a.copy_out(), b.copy_out()
+    assert np.linalg.norm(x - y) <= 8 * 2.0 ** -24 * sum(1 << len(g.targets) for g in gates)
