@@ -525,6 +525,48 @@ int launch_pass(sv_state *s, const pass::Fused &f, const char *dev) {
   return SV_OK;
 }
 
+// Sweeps of their own for items in a row, the operands of up to 64 staged by
+// one copy.
+int run_singles(sv_state *s, const std::vector<const pass::Item *> &items, int64_t *launches) {
+  std::vector<Lowered> low;
+  std::vector<size_t> off;
+  std::vector<char> ops;
+  for (size_t i = 0; i < items.size();) {
+    low.clear();
+    off.clear();
+    ops.clear();
+    size_t j = i;
+    for (; j < items.size() && j - i < 64; ++j) {
+      low.emplace_back();
+      Lowered &L = low.back();
+      const int rc = lower(s, items[j]->m, items[j]->A, items[j]->k, false, &L);
+      if (rc) return rc;
+      if (j > i && ops.size() + align256(L.op.size()) > kRingSlotBytes) break;
+      off.push_back(ops.size());
+      ops.insert(ops.end(), L.op.begin(), L.op.end());
+      ops.resize(align256(ops.size()));
+    }
+    void *dev = nullptr;
+    int slot = -1;
+    if (!ops.empty()) {
+      const int rc = stage(s, ops.data(), ops.size(), &dev, &slot);
+      if (rc) return rc;
+    }
+    const int64_t l0 = s->stats.launches;
+    for (size_t x = 0; x < j - i; ++x) {
+      const int rc = launch_lowered(s, low[x], static_cast<const char *>(dev) + off[x]);
+      if (rc) return rc;
+    }
+    *launches += s->stats.launches - l0;
+    if (slot >= 0) {
+      const int rc = release_slot(s, slot);
+      if (rc) return rc;
+    }
+    i = j;
+  }
+  return SV_OK;
+}
+
 int run_list(sv_state *s, const std::vector<SeqGate> &gates);
 
 // Runs valid gates in order through fused passes.  Sequences of narrow gates
@@ -538,14 +580,14 @@ int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
   plan_sequence(s, gates, s->L, &q);
   const sv_stats before = s->stats;
   int64_t launches = 0;
+  std::vector<const pass::Item *> singles;
   for (size_t i = 0; i < q.steps.size();) {
     if (q.steps[i].pass.S == 0) {
-      const int64_t l0 = s->stats.launches;
-      const pass::Item &it = q.items[size_t(q.steps[i].items[0])];
-      const int rc = apply_physical(s, it.m, it.A, it.k);
+      // so do the operands of single sweeps in a row
+      singles.clear();
+      for (; i < q.steps.size() && q.steps[i].pass.S == 0; ++i) singles.push_back(&q.items[size_t(q.steps[i].items[0])]);
+      const int rc = run_singles(s, singles, &launches);
       if (rc) return rc;
-      launches += s->stats.launches - l0;
-      ++i;
       continue;
     }
     // consecutive passes share a staging slot while they fit

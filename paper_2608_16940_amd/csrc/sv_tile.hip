@@ -769,12 +769,12 @@ float host_bf16_to_f(uint16_t h) {
   return f;
 }
 
-// bf16 neighbour of h one unit in the last place toward +inf (dir > 0) or -inf.
-uint16_t bf16_step(uint16_t h, int dir) {
-  const bool neg = (h & 0x8000u) != 0;
-  const uint16_t mag = h & 0x7FFFu;
-  if (mag == 0) return uint16_t(dir > 0 ? 0x0001u : 0x8001u);
-  return uint16_t((dir > 0) != neg ? h + 1 : h - 1);
+// bf16 neighbour of h one unit in the last place toward +inf or -inf, without
+// branches (their direction is random: a third of the packing's time).
+uint16_t bf16_step(uint16_t h, bool up) {
+  const int neg = h >> 15;
+  const uint16_t s = uint16_t(h + 1 - 2 * int(int(up) == neg)), z = up ? 0x0001u : 0x8001u;
+  return (h & 0x7FFFu) ? s : z;
 }
 
 // Split every component of G into bf16 hi + lo (round to nearest), then move
@@ -786,57 +786,50 @@ uint16_t bf16_step(uint16_t h, int dir) {
 // sweeps; with it diag(G'^H G') matches diag(G^H G) to far below one unit.
 // Out: hr, lr, hi_, li indexed r * D + c.
 void split_bf16x3(int D, const double *G, uint16_t *hr, uint16_t *lr, uint16_t *hi_, uint16_t *li) {
-  std::vector<double> val(2 * size_t(D)), hv(2 * size_t(D));
-  std::vector<uint16_t> l16(2 * size_t(D));
-  std::vector<char> used(2 * size_t(D));
-  for (int c = 0; c < D; ++c) {
-    double want = 0, have = 0;
+  constexpr int B = 8;  // columns at a time: eight share G's cache lines
+  std::vector<double> dl(size_t(B) * 2 * D), want(B), have(B);
+  std::vector<uint16_t> alt(size_t(B) * 2 * D);
+  for (int c0 = 0; c0 < D; c0 += B) {
+    for (int b = 0; b < B; ++b) want[b] = have[b] = 0;
     for (int r = 0; r < D; ++r)
-      for (int part = 0; part < 2; ++part) {
-        const int j = 2 * r + part;
-        const double v = part ? im_of(G, D, r, c) : re_of(G, D, r, c);
-        const uint16_t h = host_bf16_rne(float(v));
-        const double hd = host_bf16_to_f(h);
-        const uint16_t l = host_bf16_rne(float(v - hd));
-        (part ? hi_ : hr)[r * D + c] = h;
-        val[j] = v;
-        hv[j] = hd;
-        l16[j] = l;
-        used[j] = 0;
-        want += v * v;
-        const double e = hd + double(host_bf16_to_f(l));
-        have += e * e;
-      }
-    // greedy: take the re-rounding that brings the column norm closest to want
-    for (int it = 0; it < 2 * D; ++it) {
-      const double err = have - want;
-      int best = -1;
-      double best_abs = std::fabs(err), best_delta = 0;
-      uint16_t best_l = 0;
-      for (int j = 0; j < 2 * D; ++j) {
-        if (used[j]) continue;
-        const double t = val[j] - hv[j];
-        const double lcur = host_bf16_to_f(l16[j]);
-        if (lcur == t) continue;  // exact: nothing to trade
-        const uint16_t alt = bf16_step(l16[j], t > lcur ? 1 : -1);
-        const double lalt = host_bf16_to_f(alt);
-        const double e0 = hv[j] + lcur, e1 = hv[j] + lalt;
-        const double delta = e1 * e1 - e0 * e0;
-        if (std::fabs(err + delta) < best_abs) {
-          best_abs = std::fabs(err + delta);
-          best = j;
-          best_delta = delta;
-          best_l = alt;
+      for (int b = 0; b < B; ++b)
+        for (int part = 0; part < 2; ++part) {
+          const size_t i = size_t(r) * D + c0 + b;
+          const double v = G[2 * i + part];
+          const uint16_t h = host_bf16_rne(float(v));
+          const double hd = host_bf16_to_f(h), t = v - hd;
+          const uint16_t l = host_bf16_rne(float(t));
+          const double lcur = host_bf16_to_f(l), e = hd + lcur;
+          (part ? hi_ : hr)[i] = h;
+          (part ? li : lr)[i] = l;
+          want[b] += v * v;
+          have[b] += e * e;
+          const uint16_t a = bf16_step(l, t > lcur);
+          const double e1 = hd + double(host_bf16_to_f(a)), dd = e1 * e1 - e * e;
+          const size_t at = size_t(b) * 2 * D + 2 * r + part;
+          alt[at] = a;
+          dl[at] = lcur == t ? HUGE_VAL : dd;  // exact: nothing to trade
         }
+    // greedy: take the re-rounding that brings the column norm closest to want
+    for (int b = 0; b < B; ++b) {
+      double *d = dl.data() + size_t(b) * 2 * D;
+      for (int it = 0; it < 2 * D; ++it) {
+        const double err = have[b] - want[b];
+        double m[4] = {HUGE_VAL, HUGE_VAL, HUGE_VAL, HUGE_VAL};
+        for (int j = 0; j < 2 * D; j += 4)
+          for (int u = 0; u < 4; ++u) {
+            const double a = std::fabs(err + d[j + u]);
+            m[u] = a < m[u] ? a : m[u];
+          }
+        double best = m[0];
+        for (int u = 1; u < 4; ++u) best = m[u] < best ? m[u] : best;
+        if (!(best < std::fabs(err))) break;
+        int j = 0;
+        while (std::fabs(err + d[j]) != best) ++j;  // the first of equals
+        ((j & 1) ? li : lr)[size_t(j >> 1) * D + c0 + b] = alt[size_t(b) * 2 * D + j];
+        have[b] += d[j];
+        d[j] = HUGE_VAL;
       }
-      if (best < 0) break;
-      l16[best] = best_l;
-      used[best] = 1;
-      have += best_delta;
-    }
-    for (int r = 0; r < D; ++r) {
-      lr[r * D + c] = l16[2 * r];
-      li[r * D + c] = l16[2 * r + 1];
     }
   }
 }
@@ -949,11 +942,10 @@ void pack_mfma_operand(int K, int prec, const double *G, void *out) {
     for (int P = 0; P < 4; ++P)
       for (int mt = 0; mt < GMT; ++mt)
         for (int kk = 0; kk < KS; ++kk)
-          for (int l = 0; l < 64; ++l)
-            for (int e = 0; e < 8; ++e) {
-              const int r = out_row(AH, mt, l & 31), c = AH * (l >> 5) + 8 * kk + e;
-              o[((((size_t(P) * GMT + mt) * KS + kk) * 64) + l) * 8 + e] = plane[P][r * D + c];
-            }
+          for (int l = 0; l < 64; ++l) {
+            const int r = out_row(AH, mt, l & 31), c = AH * (l >> 5) + 8 * kk;
+            std::memcpy(o + ((((size_t(P) * GMT + mt) * KS + kk) * 64) + l) * 8, plane[P] + r * D + c, 16);
+          }
   } else {
     // embedding [[Re, -Im], [Im, Re]] of the split planes (split_bf16x3), hi
     // and lo planes; four consecutive reductions per step
