@@ -121,8 +121,16 @@ LayoutArg layout_arg(const sv_state *s) {
   return a;
 }
 
-// Stage `bytes` of host data into the next ring slot; returns the device pointer.
-int stage(sv_state *s, const void *host, size_t bytes, void **dev, int *slot_out) {
+struct Part {
+  const void *host;
+  size_t bytes;
+};
+
+// Stage host data into the next ring slot, each part at the next multiple of
+// 256 bytes, by one copy; returns the device pointer.
+int stage(sv_state *s, const std::vector<Part> &parts, void **dev, int *slot_out) {
+  size_t bytes = 0;
+  for (const Part &p : parts) bytes = align256(bytes) + p.bytes;
   if (bytes > kRingSlotBytes) {
     set_error("operand too large for a staging slot");
     return SV_ERR_UNSUPPORTED;
@@ -131,7 +139,12 @@ int stage(sv_state *s, const void *host, size_t bytes, void **dev, int *slot_out
   s->ring_next = (s->ring_next + 1) % kRingSlots;
   if (s->ev_live[slot]) SV_HIP_CHECK(hipEventSynchronize(s->ev[slot]));
   char *ph = s->pinned + size_t(slot) * kRingSlotBytes;
-  std::memcpy(ph, host, bytes);
+  size_t at = 0;
+  for (const Part &p : parts) {
+    at = align256(at);
+    if (p.bytes) std::memcpy(ph + at, p.host, p.bytes);
+    at += p.bytes;
+  }
   char *dv = s->ws.ring + size_t(slot) * kRingSlotBytes;
   SV_HIP_CHECK(hipMemcpyAsync(dv, ph, bytes, hipMemcpyHostToDevice, s->st));
   *dev = dv;
@@ -385,7 +398,7 @@ int apply_physical(sv_state *s, const double *matrix, const int32_t *A, int k) {
   if (L.op.empty()) return launch_lowered(s, L, nullptr);
   void *dev = nullptr;
   int slot = 0;
-  rc = stage(s, L.op.data(), L.op.size(), &dev, &slot);
+  rc = stage(s, {{L.op.data(), L.op.size()}}, &dev, &slot);
   if (rc) return rc;
   rc = launch_lowered(s, L, dev);
   if (rc) return rc;
@@ -525,31 +538,34 @@ int launch_pass(sv_state *s, const pass::Fused &f, const char *dev) {
   return SV_OK;
 }
 
-// Sweeps of their own for items in a row, the operands of up to 64 staged by
-// one copy.
+constexpr size_t kStepsAtOnce = 64;  // bounds what is held of lowered gates
+
+// Sweeps of their own for items in a row, their operands staged by one copy as
+// long as a slot takes them.
 int run_singles(sv_state *s, const std::vector<const pass::Item *> &items, int64_t *launches) {
   std::vector<Lowered> low;
+  std::vector<Part> parts;
   std::vector<size_t> off;
-  std::vector<char> ops;
+  low.reserve(std::min<size_t>(items.size(), kStepsAtOnce));
   for (size_t i = 0; i < items.size();) {
     low.clear();
+    parts.clear();
     off.clear();
-    ops.clear();
-    size_t j = i;
-    for (; j < items.size() && j - i < 64; ++j) {
+    size_t bytes = 0, j = i;
+    for (; j < items.size() && j - i < kStepsAtOnce; ++j) {
       low.emplace_back();
       Lowered &L = low.back();
       const int rc = lower(s, items[j]->m, items[j]->A, items[j]->k, false, &L);
       if (rc) return rc;
-      if (j > i && ops.size() + align256(L.op.size()) > kRingSlotBytes) break;
-      off.push_back(ops.size());
-      ops.insert(ops.end(), L.op.begin(), L.op.end());
-      ops.resize(align256(ops.size()));
+      if (j > i && bytes + align256(L.op.size()) > kRingSlotBytes) break;
+      off.push_back(bytes);
+      parts.push_back({L.op.data(), L.op.size()});
+      bytes += align256(L.op.size());
     }
     void *dev = nullptr;
     int slot = -1;
-    if (!ops.empty()) {
-      const int rc = stage(s, ops.data(), ops.size(), &dev, &slot);
+    if (bytes) {
+      const int rc = stage(s, parts, &dev, &slot);
       if (rc) return rc;
     }
     const int64_t l0 = s->stats.launches;
@@ -599,12 +615,11 @@ int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
       bytes += align256(q.steps[j].pass.data.size());
       ++j;
     }
-    std::vector<char> host(bytes);
-    for (size_t x = i; x < j; ++x)
-      std::memcpy(host.data() + off[x - i], q.steps[x].pass.data.data(), q.steps[x].pass.data.size());
+    std::vector<Part> parts;
+    for (size_t x = i; x < j; ++x) parts.push_back({q.steps[x].pass.data.data(), q.steps[x].pass.data.size()});
     void *dev = nullptr;
     int slot = 0;
-    int rc = stage(s, host.data(), bytes, &dev, &slot);
+    int rc = stage(s, parts, &dev, &slot);
     if (rc) return rc;
     for (size_t x = i; x < j; ++x) {
       rc = launch_pass(s, q.steps[x].pass, static_cast<const char *>(dev) + off[x - i]);
@@ -641,49 +656,49 @@ int run_chains(sv_state *s, const std::vector<SeqGate> &gates) {
   std::vector<chain::Step> steps = chain::build(s->n, q.items);
   const sv_stats before = s->stats;
   int64_t launches = 0;
-  std::vector<char> ops;
   std::vector<Lowered> single;
+  std::vector<std::vector<char>> fused;
+  std::vector<Part> parts;
   std::vector<size_t> off;
-  constexpr size_t kStepsAtOnce = 64;
+  single.reserve(std::min(steps.size(), kStepsAtOnce));
   for (size_t i = 0; i < steps.size();) {
     // operands of steps [i, j), as many as a staging slot takes
-    ops.clear();
     single.clear();
+    fused.clear();
+    parts.clear();
     off.clear();
     const size_t i0 = i;
-    size_t j = i;
+    size_t j = i, bytes = 0;
     for (; j < steps.size() && j - i0 < kStepsAtOnce; ++j) {
       chain::Step &x = steps[j];
-      size_t bytes = 0;
       single.emplace_back();
-      Lowered &one = single.back();
+      fused.emplace_back();
+      Part part;
       if (!x.fused) {
         const pass::Item &g = q.items[size_t(x.items[0])];
-        const int rc = lower(s, g.m, g.A, g.k, false, &one);
+        const int rc = lower(s, g.m, g.A, g.k, false, &single.back());
         if (rc) return rc;
-        bytes = align256(one.op.size());
+        part = {single.back().op.data(), single.back().op.size()};
       } else {
-        for (int g : x.items) bytes += align256(mfma_operand_bytes(q.items[size_t(g)].k, s->prec));
+        std::vector<char> &ops = fused.back();
+        for (size_t g = 0; g < x.items.size(); ++g) {
+          const pass::Item &y = q.items[size_t(x.items[g])];
+          const size_t at = ops.size();
+          x.gate[g].op = int32_t(at);
+          ops.resize(at + align256(mfma_operand_bytes(y.k, s->prec)));
+          pack_mfma_operand(y.k, s->prec, y.m, ops.data() + at);
+        }
+        part = {ops.data(), ops.size()};
       }
-      if (j > i && ops.size() + bytes > kRingSlotBytes) break;
-      off.push_back(ops.size());
-      ops.resize(off.back() + bytes);
-      if (!x.fused) {
-        if (bytes) std::memcpy(ops.data() + off.back(), one.op.data(), one.op.size());
-        continue;
-      }
-      size_t at = 0;
-      for (size_t g = 0; g < x.items.size(); ++g) {
-        const pass::Item &y = q.items[size_t(x.items[g])];
-        pack_mfma_operand(y.k, s->prec, y.m, ops.data() + off.back() + at);
-        x.gate[g].op = int32_t(at);
-        at += align256(mfma_operand_bytes(y.k, s->prec));
-      }
+      if (j > i && bytes + align256(part.bytes) > kRingSlotBytes) break;
+      off.push_back(bytes);
+      parts.push_back(part);
+      bytes += align256(part.bytes);
     }
     void *dev = nullptr;
     int slot = -1;
-    if (!ops.empty()) {
-      const int rc = stage(s, ops.data(), ops.size(), &dev, &slot);
+    if (bytes) {
+      const int rc = stage(s, parts, &dev, &slot);
       if (rc) return rc;
     }
     for (; i < j; ++i) {

@@ -745,9 +745,10 @@ hipError_t launch_probs(const float2 *psi, int n, double *out, int logical, cons
   bool moved = false;
   for (int q = 0; q < n; ++q) moved = moved || L.pos[q] != q;
   if (!moved) logical = 0;  // the identity layout: both orders are one
-  // the tile kernel from 2^12 amplitudes, where it exists, to any; the map per amplitude below and for
-  // an output that 16-byte stores do not fit
-  if (logical && n >= 12 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) return launch_probs_tile(psi, n, out, L, st);
+  // The tile kernel from 2^19 amplitudes on (n=18 5.1 us and 3.8 by the map per amplitude, n=19 5.4 and
+  // 6.2, n=22 15.9 and 44.6); the map below, where the state sits in the caches, and for an output that
+  // 16-byte stores do not fit.
+  if (logical && n >= 19 && (reinterpret_cast<uintptr_t>(out) & 15) == 0) return launch_probs_tile(psi, n, out, L, st);
   hipLaunchKernelGGL(k_probs, dim3(grid_for(dim, kThreads, kFullGrid)), dim3(kThreads), 0, st, psi, dim, n, out,
                      logical, L);
   return hipGetLastError();

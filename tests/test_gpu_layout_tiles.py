@@ -40,7 +40,7 @@ def test_layout_moves_every_amplitude(n):
     sv.close()
 
 
-@pytest.mark.parametrize("n", [11, 12, 13, 18, 24])
+@pytest.mark.parametrize("n", [11, 12, 13, 18, 19, 20, 24])
 def test_logical_probabilities_are_exact(n):
     import torch
     rng = np.random.default_rng(100 + n)
