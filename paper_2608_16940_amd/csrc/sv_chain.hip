@@ -7,8 +7,8 @@
 // every amplitude is the same bit for bit; only where the groups sit differs.
 //
 // Bound by the matrix cores where a six-bit gate is in the chain, by memory
-// otherwise: at 2^26 amplitudes two four-bit gates take 240 us (one 171 alone;
-// 181 us of memory, 110 of products), a six- and a four-bit one 372 (262 +
+// otherwise: at 2^26 amplitudes two four-bit gates take 222 us (one 171 alone;
+// 181 us of memory, 110 of products), a six- and a four-bit one 352 (262 +
 // 171), two six-bit ones 473 to 550 (the products alone 343).  Two workgroups of
 // four waves per CU, one tile each, cover each other's loads and stores; a
 // persistent grid that held the next tile in registers was 5% slower (the wait
@@ -32,7 +32,7 @@ constexpr int kChunks = (1 << kTileBits) / 2 / kThreads;  // of 16 bytes per thr
 struct Args {
   float2 *psi;
   const char *ops;
-  int32_t ngates;
+  int32_t ngates, cus;
   int32_t sbit[kTileBits];
   Gate gate[kMaxGates];
 };
@@ -248,6 +248,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_chain(Args a) {
   };
   auto end = [&]() __attribute__((always_inline)) { __syncthreads(); };
 
+  // The second workgroup of each CU starts a few microseconds late, so that one
+  // loads or stores while the other multiplies: in step, both wait for memory
+  // at once (two four-bit gates 236 -> 222 us, a six- and a four-bit one 370 ->
+  // 352 at 2^26 amplitudes; two six-bit ones unchanged).  cus: 0 for small states.
+  if (int(blockIdx.x) >= a.cus && int(blockIdx.x) < 2 * a.cus) __builtin_amdgcn_s_sleep(127);
   const int64_t base = tile_base(blockIdx.x) + goff;
   {
     floatx4 v[kChunks];
@@ -291,6 +296,9 @@ hipError_t launch(int n, const Step &s, float2 *psi, const char *ops, hipStream_
     a.gate[i] = i < a.ngates ? s.gate[i] : Gate{};
     if (i < a.ngates && (a.gate[i].K < 4 || a.gate[i].K > 6)) return hipErrorInvalidValue;
   }
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  a.cus = (1 << (n - kTileBits)) >= 8 * cus ? cus : 0;  // with few tiles per CU the start costs more than it gives
   hipLaunchKernelGGL(k_chain, dim3(1u << (n - kTileBits)), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }

@@ -104,9 +104,7 @@ __global__ __launch_bounds__(kThreadsMax) void k_prog(const Args by_value, float
     words[i] = ((const uint32_t __attribute__((address_space(4))) *)a)[i];
   const Args *prog = reinterpret_cast<const Args *>(words);
   // Below ten tile bits there are fewer threads' worth than a wave has lanes:
-  // the others repeat them, in step with them.  No branch of the kernel
-  // diverges, so that the op switch stays one of scalar branches (with
-  // divergent ones inside, every op's way through it copied the registers).
+  // the others repeat them, in step with them, so that no branch diverges.
   const int S = a->S, T = 1 << (S - kRegBits), tid = threadIdx.x & (T - 1);
   uint64_t base = blockIdx.x;   // the tile's physical index, tile bits zero
   for (int b = 0; b < S; ++b) {
