@@ -488,6 +488,7 @@ bool resolve_gate(int n, const SeqGate &g, int32_t *L, sv_stats *add, pass::Item
     }
     const DiagCover cv = diag_cover(g.k, dd, it->A);
     it->sweep = double(cv.nsub) * kDiagLaunchCost;
+    it->launches = cv.nsub;
     for (int i = 0; i < cv.nsub; ++i) {
       const int f = __builtin_popcount(cv.mask[i]);
       it->sweep += std::ldexp(1.0, -f);
@@ -498,6 +499,7 @@ bool resolve_gate(int n, const SeqGate &g, int32_t *L, sv_stats *add, pass::Item
   }
   it->exact = false;
   it->sweep = 1.0;
+  it->launches = 1;
   if (g.k == 1 && it->A[0] <= 6)
     v = SV_VARIANT_SHUFFLE;
   else if (g.k >= 4 && g.k <= 7 && n >= g.k + mfma_tile_M(g.k))

@@ -516,8 +516,14 @@ std::vector<Step> build_steps(int n, const std::vector<Item> &items, int prec) {
     Draft d = B.draft(done, from);
     B.trim(d, done);
     // one gate, or diagonals alone whose partial sweeps cost less than a pass
+    // (on small states, where a launch of 3 us is all they cost, three of them
+    // against the 9 us of a pass)
     double alone = 0.0;
-    for (int i : d.items) alone += items[size_t(i)].sweep;
+    int launches = 0;
+    for (int i : d.items) {
+      alone += items[size_t(i)].sweep;
+      launches += items[size_t(i)].launches;
+    }
     Step s;
     if (d.items.empty()) {  // tables that cannot fit on their own
       single(int(from));
@@ -525,7 +531,7 @@ std::vector<Step> build_steps(int n, const std::vector<Item> &items, int prec) {
       continue;
     }
     const bool lone = d.items.size() == 1 && items[size_t(d.items[0])].k != 6;
-    if (lone || (d.dense.empty() && alone <= 1.1) || !B.emit(d, &s.pass)) {
+    if (lone || (d.dense.empty() && (alone <= 1.1 || (n <= 18 && launches <= 3))) || !B.emit(d, &s.pass)) {
       for (int i : d.items) single(i);
       continue;
     }

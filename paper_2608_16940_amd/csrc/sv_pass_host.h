@@ -68,6 +68,7 @@ struct Item {
   bool diag = false;
   bool exact = false;  // diagonal with entries 1, -1, i, -i only
   double sweep = 1.0;  // share of a full sweep (plus launches) it costs on its own
+  int launches = 1;    // on its own
 };
 
 struct Fused {
