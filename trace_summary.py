@@ -35,7 +35,7 @@ def main(argv):
              "|---|---:|---:|---:|---:|---:|---:|---:|"]
     for r in sorted(rows, key=lambda r: -float(col(r, "TotalDurationNs", "TotalDuration"))):
         name = col(r, "Name", "KernelName")
-        short = name.replace("sv::(anonymous namespace)::", "").replace("sv::", "")
+        short = name.replace("(anonymous namespace)::", "").replace("sv::", "")
         if short.startswith("void "):
             short = short[5:]
         short = short.split("(")[0]
