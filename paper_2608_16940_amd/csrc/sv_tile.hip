@@ -770,7 +770,8 @@ float host_bf16_to_f(uint16_t h) {
 }
 
 // bf16 neighbour of h one unit in the last place toward +inf or -inf, without
-// branches (their direction is random: a third of the packing's time).
+// branches: their direction is random (a seven-qubit split 1.0 ms with them,
+// 0.48 without).
 uint16_t bf16_step(uint16_t h, bool up) {
   const int neg = h >> 15;
   const uint16_t s = uint16_t(h + 1 - 2 * int(int(up) == neg)), z = up ? 0x0001u : 0x8001u;
