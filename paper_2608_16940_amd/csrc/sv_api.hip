@@ -6,6 +6,7 @@
 #include <climits>
 #include <memory>
 #include <utility>
+#include <variant>
 #include <cstdio>
 #include <cstring>
 #include <string>
@@ -531,59 +532,82 @@ void finish_sequence(sv_state *s, const Sequence &q, const std::vector<SeqGate> 
   }
 }
 
-int launch_pass(sv_state *s, const pass::Fused &f, const char *dev) {
-  const hipError_t e = pass::launch(s->n, f, s->amps, dev, s->st);
+// One launch of a sequence (a diagonal gate's few): a gate's own sweep, a fused
+// pass or a gate chain, and the operand it reads in device memory.
+struct Step {
+  std::variant<Lowered, pass::Fused, chain::Step> what;
+  std::vector<char> op;
+};
+
+int gate_step(const sv_state *s, const pass::Item &it, Step *st) {
+  Lowered &L = st->what.emplace<Lowered>();
+  const int rc = lower(s, it.m, it.A, it.k, false, &L);
+  st->op = std::move(L.op);
+  return rc;
+}
+
+void pass_step(pass::Fused &&f, Step *st) {
+  st->op = std::move(f.data);
+  st->what = std::move(f);
+}
+
+// dev: the step's operand in device memory.
+int launch_step(sv_state *s, const Step &st, const char *dev) {
+  if (const Lowered *L = std::get_if<Lowered>(&st.what)) return launch_lowered(s, *L, dev);
+  const pass::Fused *f = std::get_if<pass::Fused>(&st.what);
+  const hipError_t e = f ? pass::launch(s->n, *f, s->amps, dev, s->st)
+                         : chain::launch(s->n, std::get<chain::Step>(st.what), s->amps, dev, s->st);
   if (e != hipSuccess) {
     set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
     return SV_ERR_DEVICE;
   }
+  s->stats.launches += 1;
   return SV_OK;
 }
 
-constexpr size_t kStepsAtOnce = 64;  // bounds what is held of lowered gates
+// Launches steps in order.  Steps are held until their operands fill a staging
+// slot, which one copy stages; a step that no longer fits opens the next one.
+class Runner {
+ public:
+  explicit Runner(sv_state *s) : s_(s) {}
 
-// Sweeps of their own for items in a row, their operands staged by one copy as
-// long as a slot takes them.
-int run_singles(sv_state *s, const std::vector<const pass::Item *> &items, int64_t *launches) {
-  std::vector<Lowered> low;
-  std::vector<Part> parts;
-  std::vector<size_t> off;
-  low.reserve(std::min<size_t>(items.size(), kStepsAtOnce));
-  for (size_t i = 0; i < items.size();) {
-    low.clear();
-    parts.clear();
-    off.clear();
-    size_t bytes = 0, j = i;
-    for (; j < items.size() && j - i < kStepsAtOnce; ++j) {
-      low.emplace_back();
-      Lowered &L = low.back();
-      const int rc = lower(s, items[j]->m, items[j]->A, items[j]->k, false, &L);
+  int push(Step &&st) {
+    const size_t bytes = align256(st.op.size());
+    if (!held_.empty() && (held_.size() == kHeldMax || bytes_ + bytes > kRingSlotBytes)) {
+      const int rc = flush();
       if (rc) return rc;
-      if (j > i && bytes + align256(L.op.size()) > kRingSlotBytes) break;
-      off.push_back(bytes);
-      parts.push_back({L.op.data(), L.op.size()});
-      bytes += align256(L.op.size());
     }
+    bytes_ += bytes;
+    held_.push_back(std::move(st));
+    return SV_OK;
+  }
+
+  int flush() {
     void *dev = nullptr;
     int slot = -1;
-    if (bytes) {
-      const int rc = stage(s, parts, &dev, &slot);
+    if (bytes_) {
+      std::vector<Part> parts;
+      for (const Step &st : held_) parts.push_back({st.op.data(), st.op.size()});
+      const int rc = stage(s_, parts, &dev, &slot);
       if (rc) return rc;
     }
-    const int64_t l0 = s->stats.launches;
-    for (size_t x = 0; x < j - i; ++x) {
-      const int rc = launch_lowered(s, low[x], static_cast<const char *>(dev) + off[x]);
+    size_t at = 0;
+    for (const Step &st : held_) {
+      const int rc = launch_step(s_, st, static_cast<const char *>(dev) + at);
       if (rc) return rc;
+      at += align256(st.op.size());
     }
-    *launches += s->stats.launches - l0;
-    if (slot >= 0) {
-      const int rc = release_slot(s, slot);
-      if (rc) return rc;
-    }
-    i = j;
+    held_.clear();
+    bytes_ = 0;
+    return slot >= 0 ? release_slot(s_, slot) : SV_OK;
   }
-  return SV_OK;
-}
+
+ private:
+  static constexpr size_t kHeldMax = 64;
+  sv_state *s_;
+  std::vector<Step> held_;
+  size_t bytes_ = 0;
+};
 
 int run_list(sv_state *s, const std::vector<SeqGate> &gates);
 
@@ -597,43 +621,22 @@ int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
   Sequence q;
   plan_sequence(s, gates, s->L, &q);
   const sv_stats before = s->stats;
-  int64_t launches = 0;
-  std::vector<const pass::Item *> singles;
-  for (size_t i = 0; i < q.steps.size();) {
-    if (q.steps[i].pass.S == 0) {
-      // so do the operands of single sweeps in a row
-      singles.clear();
-      for (; i < q.steps.size() && q.steps[i].pass.S == 0; ++i) singles.push_back(&q.items[size_t(q.steps[i].items[0])]);
-      const int rc = run_singles(s, singles, &launches);
+  Runner run(s);
+  for (pass::Step &x : q.steps) {
+    Step st;
+    if (x.pass.S > 0) {
+      pass_step(std::move(x.pass), &st);
+    } else {
+      const int rc = gate_step(s, q.items[size_t(x.items[0])], &st);
       if (rc) return rc;
-      continue;
     }
-    // consecutive passes share a staging slot while they fit
-    size_t j = i, bytes = 0;
-    std::vector<size_t> off;
-    while (j < q.steps.size() && q.steps[j].pass.S > 0 &&
-           (j == i || bytes + align256(q.steps[j].pass.data.size()) <= kRingSlotBytes)) {
-      off.push_back(bytes);
-      bytes += align256(q.steps[j].pass.data.size());
-      ++j;
-    }
-    std::vector<Part> parts;
-    for (size_t x = i; x < j; ++x) parts.push_back({q.steps[x].pass.data.data(), q.steps[x].pass.data.size()});
-    void *dev = nullptr;
-    int slot = 0;
-    int rc = stage(s, parts, &dev, &slot);
+    const int rc = run.push(std::move(st));
     if (rc) return rc;
-    for (size_t x = i; x < j; ++x) {
-      rc = launch_pass(s, q.steps[x].pass, static_cast<const char *>(dev) + off[x - i]);
-      if (rc) return rc;
-      ++launches;
-    }
-    rc = release_slot(s, slot);
-    if (rc) return rc;
-    i = j;
   }
+  const int rc = run.flush();
+  if (rc) return rc;
+  q.add.launches = s->stats.launches - before.launches;
   s->stats = before;
-  q.add.launches = launches;
   add_stats(&s->stats, q.add);
   finish_sequence(s, q, gates);
   return SV_OK;
@@ -646,8 +649,7 @@ bool chainable(const sv_state *s) {
          s->opsrc == SV_MFMA_OPERAND_AUTO && s->tile_order == -1 && s->prec == SV_PREC_FP32;
 }
 
-// Runs valid gates in order as chains and single sweeps.  The operands of
-// steps that follow each other are staged together.
+// Runs valid gates in order as chains and single sweeps.
 int run_chains(sv_state *s, const std::vector<SeqGate> &gates) {
   Sequence q;
   std::memset(&q.add, 0, sizeof(q.add));
@@ -655,77 +657,30 @@ int run_chains(sv_state *s, const std::vector<SeqGate> &gates) {
   pass::Item it;
   for (const SeqGate &g : gates)
     if (resolve_gate(s->n, g, q.Lend, &q.add, &it)) q.items.push_back(it);
-  std::vector<chain::Step> steps = chain::build(s->n, q.items);
   const sv_stats before = s->stats;
-  int64_t launches = 0;
-  std::vector<Lowered> single;
-  std::vector<std::vector<char>> fused;
-  std::vector<Part> parts;
-  std::vector<size_t> off;
-  single.reserve(std::min(steps.size(), kStepsAtOnce));
-  for (size_t i = 0; i < steps.size();) {
-    // operands of steps [i, j), as many as a staging slot takes
-    single.clear();
-    fused.clear();
-    parts.clear();
-    off.clear();
-    const size_t i0 = i;
-    size_t j = i, bytes = 0;
-    for (; j < steps.size() && j - i0 < kStepsAtOnce; ++j) {
-      chain::Step &x = steps[j];
-      single.emplace_back();
-      fused.emplace_back();
-      Part part;
-      if (!x.fused) {
-        const pass::Item &g = q.items[size_t(x.items[0])];
-        const int rc = lower(s, g.m, g.A, g.k, false, &single.back());
-        if (rc) return rc;
-        part = {single.back().op.data(), single.back().op.size()};
-      } else {
-        std::vector<char> &ops = fused.back();
-        for (size_t g = 0; g < x.items.size(); ++g) {
-          const pass::Item &y = q.items[size_t(x.items[g])];
-          const size_t at = ops.size();
-          x.gate[g].op = int32_t(at);
-          ops.resize(at + align256(mfma_operand_bytes(y.k, s->prec)));
-          pack_mfma_operand(y.k, s->prec, y.m, ops.data() + at);
-        }
-        part = {ops.data(), ops.size()};
-      }
-      if (j > i && bytes + align256(part.bytes) > kRingSlotBytes) break;
-      off.push_back(bytes);
-      parts.push_back(part);
-      bytes += align256(part.bytes);
-    }
-    void *dev = nullptr;
-    int slot = -1;
-    if (bytes) {
-      const int rc = stage(s, parts, &dev, &slot);
+  Runner run(s);
+  for (chain::Step &x : chain::build(s->n, q.items)) {
+    Step st;
+    if (!x.fused) {
+      const int rc = gate_step(s, q.items[size_t(x.items[0])], &st);
       if (rc) return rc;
-    }
-    for (; i < j; ++i) {
-      const char *data = static_cast<const char *>(dev) + off[i - i0];
-      if (!steps[i].fused) {
-        const int64_t l0 = s->stats.launches;
-        const int rc = launch_lowered(s, single[i - i0], data);
-        if (rc) return rc;
-        launches += s->stats.launches - l0;
-        continue;
+    } else {
+      for (size_t g = 0; g < x.items.size(); ++g) {
+        const pass::Item &y = q.items[size_t(x.items[g])];
+        const size_t at = st.op.size();
+        x.gate[g].op = int32_t(at);
+        st.op.resize(at + align256(mfma_operand_bytes(y.k, s->prec)));
+        pack_mfma_operand(y.k, s->prec, y.m, st.op.data() + at);
       }
-      const hipError_t e = chain::launch(s->n, steps[i], s->amps, data, s->st);
-      if (e != hipSuccess) {
-        set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
-        return SV_ERR_DEVICE;
-      }
-      ++launches;
+      st.what = std::move(x);
     }
-    if (slot >= 0) {
-      const int rc = release_slot(s, slot);
-      if (rc) return rc;
-    }
+    const int rc = run.push(std::move(st));
+    if (rc) return rc;
   }
+  const int rc = run.flush();
+  if (rc) return rc;
+  q.add.launches = s->stats.launches - before.launches;
   s->stats = before;
-  q.add.launches = launches;
   add_stats(&s->stats, q.add);
   finish_sequence(s, q, gates);
   return SV_OK;
@@ -1299,10 +1254,8 @@ int sv_get_stats(const sv_state *s, sv_stats *out) {
 }  // extern "C"
 
 // ------------------------------------------------------------------ bound plans
-// One launch of a bound plan: a fused pass (pass.S > 0) or a lowered gate.
 struct BoundStep {
-  Lowered gate;
-  pass::Fused pass;
+  Step step;
   size_t off = SIZE_MAX;  // operand offset in op_dev (SIZE_MAX: by value)
 };
 
@@ -1342,53 +1295,52 @@ int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
     gates.push_back({k.matrix.data(), k.tuple.data(), k.k});
   }
   size_t total = 0;
-  auto take = [&](BoundStep &st, size_t n) {
-    st.off = total;
-    total += align256(n);
-  };
-  auto add_gate = [&](const double *m, const int32_t *A, int k) -> int {
-    BoundStep st;
-    const int rc = lower(s, m, A, k, false, &st.gate);
-    if (rc) return rc;
-    if (!st.gate.op.empty()) take(st, st.gate.op.size());
-    b->per_run.launches += st.gate.variant == SV_VARIANT_DIAG ? st.gate.cover.nsub : 1;
-    b->steps.push_back(std::move(st));
-    return SV_OK;
+  auto add = [&](Step &&st) {
+    BoundStep x;
+    x.step = std::move(st);
+    if (!x.step.op.empty()) {
+      x.off = total;
+      total += align256(x.step.op.size());
+    }
+    const Lowered *L = std::get_if<Lowered>(&x.step.what);
+    b->per_run.launches += L && L->variant == SV_VARIANT_DIAG ? L->cover.nsub : 1;
+    b->steps.push_back(std::move(x));
   };
   if (fusible(s)) {
     Sequence q;
     plan_sequence(s, gates, s->L, &q);
     b->per_run = q.add;
     for (pass::Step &x : q.steps) {
-      if (x.pass.S == 0) {
-        const pass::Item &it = q.items[size_t(x.items[0])];
-        const int rc = add_gate(it.m, it.A, it.k);
+      Step st;
+      if (x.pass.S > 0) {
+        pass_step(std::move(x.pass), &st);
+      } else {
+        const int rc = gate_step(s, q.items[size_t(x.items[0])], &st);
         if (rc) return rc;
-        continue;
       }
-      BoundStep st;
-      st.pass = std::move(x.pass);
-      take(st, st.pass.data.size());
-      b->per_run.launches += 1;
-      b->steps.push_back(std::move(st));
+      add(std::move(st));
     }
     std::memcpy(b->Lend, q.Lend, sizeof(b->Lend));
   } else {
+    pass::Item it;
     for (const SeqGate &g : gates) {
-      int32_t A[SV_MAX_K];
-      for (int j = 0; j < g.k; ++j) A[j] = b->Lend[g.t[j]];
+      it.k = g.k;
+      it.m = g.m;
+      for (int j = 0; j < g.k; ++j) it.A[j] = b->Lend[g.t[j]];
       int perm[SV_MAX_K];
       if (s->variant == SV_VARIANT_AUTO && qubit_permutation(g.m, g.k, perm)) {  // as sv_apply_fused
-        for (int j = 0; j < g.k; ++j) b->Lend[g.t[perm[j]]] = A[j];
+        for (int j = 0; j < g.k; ++j) b->Lend[g.t[perm[j]]] = it.A[j];
         b->per_run.layout_only += 1;
         continue;
       }
-      const int rc = add_gate(g.m, A, g.k);
+      Step st;
+      const int rc = gate_step(s, it, &st);
       if (rc) return rc;
-      const Lowered &L = b->steps.back().gate;
+      const Lowered &L = std::get<Lowered>(st.what);
       b->per_run.gate_sweeps += 1;
       if (L.variant < 6) b->per_run.by_variant[L.variant] += 1;
       if (L.variant == SV_VARIANT_DIAG) b->per_run.diag_chunks += diag_chunks(L, s->n);
+      add(std::move(st));
     }
   }
   *bytes = total;
@@ -1410,7 +1362,7 @@ int bound_check(const sv_bound *b) {
 int bound_launch_all(sv_bound *b) {
   for (const BoundStep &st : b->steps) {
     const char *dev = st.off == SIZE_MAX ? nullptr : b->op_dev + st.off;
-    const int rc = st.pass.S > 0 ? launch_pass(b->s, st.pass, dev) : launch_lowered(b->s, st.gate, dev);
+    const int rc = launch_step(b->s, st.step, dev);
     if (rc) return rc;
   }
   return SV_OK;
@@ -1529,7 +1481,7 @@ int sv_plan_bind(sv_state *s, const sv_plan *p, void *op_dev, size_t op_bytes, s
     std::vector<char> host(need);
     for (BoundStep &st : b->steps) {
       if (st.off == SIZE_MAX) continue;
-      std::vector<char> &src = st.pass.S > 0 ? st.pass.data : st.gate.op;
+      std::vector<char> &src = st.step.op;
       std::memcpy(host.data() + st.off, src.data(), src.size());
       src.clear();
       src.shrink_to_fit();

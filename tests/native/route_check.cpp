@@ -1,0 +1,175 @@
+// What the library's entry points ask of the GPU, checked on the host (see
+// host_runtime.h): which kernels a call launches and when, what it packs and
+// copies for them, and what a failed launch leaves.  The argument names a check.
+#include "host_runtime.h"
+
+#include <cmath>
+#include <cstdint>
+#include <cstring>
+#include <functional>
+#include <random>
+
+#include "sv.h"
+#include "sv_density.h"
+#include "sv_plan.h"
+
+namespace {
+
+int failures = 0;
+
+#define CHECK(cond, ...)                                    \
+  do {                                                      \
+    if (!(cond)) {                                          \
+      std::printf("%s:%d: %s: ", __FILE__, __LINE__, #cond); \
+      std::printf(__VA_ARGS__);                             \
+      std::printf("\n");                                    \
+      ++failures;                                           \
+    }                                                       \
+  } while (0)
+
+struct Gate {
+  std::vector<int32_t> t;
+  std::vector<double> m;
+};
+
+std::mt19937 rng(7);
+
+double uniform() { return std::uniform_real_distribution<double>(-1.0, 1.0)(rng); }
+
+// A dense matrix: what it holds does not matter to the host.
+Gate dense(const std::vector<int32_t> &t) {
+  Gate g{t, std::vector<double>(size_t(2) << (2 * t.size()))};
+  for (double &x : g.m) x = uniform();
+  return g;
+}
+
+Gate diagonal(const std::vector<int32_t> &t) {
+  const size_t D = size_t(1) << t.size();
+  Gate g{t, std::vector<double>(2 * D * D, 0.0)};
+  for (size_t r = 0; r < D; ++r) {
+    const double a = uniform() * 3.0;
+    g.m[2 * (r * D + r)] = std::cos(a);
+    g.m[2 * (r * D + r) + 1] = std::sin(a);
+  }
+  return g;
+}
+
+Gate swap(int32_t a, int32_t b) {
+  Gate g{{a, b}, std::vector<double>(32, 0.0)};
+  const int one[4] = {0, 2, 1, 3};
+  for (int c = 0; c < 4; ++c) g.m[size_t(2 * (one[c] * 4 + c))] = 1.0;
+  return g;
+}
+
+std::vector<int32_t> targets(int n, int k) {
+  std::vector<int32_t> all(static_cast<size_t>(n));
+  for (int i = 0; i < n; ++i) all[size_t(i)] = i;
+  std::shuffle(all.begin(), all.end(), rng);
+  all.resize(size_t(k));
+  return all;
+}
+
+std::vector<int32_t> window(int n, int k) {
+  std::vector<int32_t> t(static_cast<size_t>(k));
+  const int s = std::uniform_int_distribution<int>(0, n - k)(rng);
+  for (int i = 0; i < k; ++i) t[size_t(i)] = s + i;
+  return t;
+}
+
+// A plan whose blocks are the given gates, one each (the cap is below every width).
+sv_plan *plan_of(int n, const std::vector<Gate> &gates) {
+  std::vector<int32_t> ks, ts;
+  std::vector<double> ms;
+  std::vector<int8_t> dg(gates.size(), 0);
+  for (const Gate &g : gates) {
+    ks.push_back(int32_t(g.t.size()));
+    ts.insert(ts.end(), g.t.begin(), g.t.end());
+    ms.insert(ms.end(), g.m.begin(), g.m.end());
+  }
+  sv_plan *p = nullptr;
+  const int rc = sv_plan_greedy(n, int(gates.size()), ks.data(), ts.data(), ms.data(), dg.data(), 1, &p);
+  int nb = 0;
+  sv_plan_num_blocks(p, &nb);
+  CHECK(rc == SV_OK && nb == int(gates.size()), "rc %d, %d blocks of %zu gates", rc, nb, gates.size());
+  return p;
+}
+
+void *const kAmps = reinterpret_cast<void *>(uintptr_t(1) << 40);
+void *const kWork = reinterpret_cast<void *>(uintptr_t(1) << 44);
+void *const kOps = reinterpret_cast<void *>(uintptr_t(1) << 45);
+
+sv_state *state(int n) {
+  sv_state *s = nullptr;
+  const int rc = sv_alloc(&s, n, kAmps, size_t(8) << n, kWork, sv_workspace_bytes(n), nullptr);
+  CHECK(rc == SV_OK, "sv_alloc %d: %s", rc, sv_last_error());
+  return s;
+}
+
+int apply_list(sv_state *s, const std::vector<Gate> &gates) {
+  std::vector<int32_t> ks, ts;
+  std::vector<double> ms;
+  for (const Gate &g : gates) {
+    ks.push_back(int32_t(g.t.size()));
+    ts.insert(ts.end(), g.t.begin(), g.t.end());
+    ms.insert(ms.end(), g.m.begin(), g.m.end());
+  }
+  return sv_apply_gates(s, int64_t(gates.size()), ks.data(), ts.data(), ms.data());
+}
+
+std::vector<int32_t> layout(sv_state *s, int n) {
+  std::vector<int32_t> L(static_cast<size_t>(n));
+  sv_get_layout(s, L.data());
+  return L;
+}
+
+size_t count(const std::string &kernel) {
+  size_t c = 0;
+  for (const std::string &k : rt::launched()) c += k == kernel;
+  return c;
+}
+
+// ---------------------------------------------------------------- checks
+// An operand is packed once, also where a staging slot is full before it.
+void packed_once() {
+  const int n = 24;
+  for (int k : {6, 7}) {
+    std::vector<Gate> gates;
+    for (int i = 0; i < 40; ++i) gates.push_back(dense(targets(n, k)));
+    for (int prec : {SV_PREC_FP32, SV_PREC_BF16X3}) {
+      if (k == 6 && prec == SV_PREC_FP32) continue;  // those run in passes
+      sv_state *s = state(n);
+      sv_set_option(s, SV_OPT_PRECISION, prec);
+      sv_plan *p = plan_of(n, gates);
+      rt::start();
+      CHECK(sv_run_plan(s, p) == SV_OK, "%s", sv_last_error());
+      rt::stop();
+      size_t copied = 0;
+      for (const rt::Event &e : rt::events()) copied += e.bytes;
+      CHECK(rt::launched().size() == gates.size(), "%zu launches", rt::launched().size());
+      // the split of a BF16x3 operand works in a few planes of the matrix besides; 8 KiB a gate for its descriptors
+      const double want = (prec == SV_PREC_BF16X3 ? 2.2 : 1.1) * double(copied) + 8192.0 * double(gates.size());
+      CHECK(double(rt::allocated) < want, "k=%d prec=%d: %zu allocated for %zu of operands", k, prec, rt::allocated, copied);
+      sv_plan_free(p);
+      sv_free(s);
+    }
+  }
+}
+
+const std::map<std::string, std::function<void()>> kChecks = {
+    {"packed_once", packed_once},
+};
+
+}  // namespace
+
+int main(int argc, char **argv) {
+  for (int i = 1; i < argc; ++i) {
+    const auto it = kChecks.find(argv[i]);
+    if (it == kChecks.end()) {
+      std::printf("no check %s\n", argv[i]);
+      return 2;
+    }
+    it->second();
+  }
+  if (failures == 0) std::printf("route checks passed\n");
+  return failures != 0;
+}
