@@ -565,17 +565,25 @@ int launch_step(sv_state *s, const Step &st, const char *dev) {
   return SV_OK;
 }
 
-// Launches steps in order.  Steps are held until their operands fill a staging
-// slot, which one copy stages; a step that no longer fits opens the next one.
+// Launches steps in order.  Operands of steps that follow each other are staged
+// by one copy, which costs some 15 us on the host and on the device.  Steps are
+// held until a slot is full; a step that no longer fits opens the next one.
+// Seven-qubit operands, which take longest to pack, start with two, so that the
+// device has work meanwhile (four such gates on 8 qubits from an idle stream:
+// 267 us held to a full slot, 182 in pairs; plans of five- and six-qubit gates
+// lose by an earlier copy, 154 to 175 us for two layers on a 10-qubit density
+// matrix).
 class Runner {
  public:
   explicit Runner(sv_state *s) : s_(s) {}
 
-  int push(Step &&st) {
-    const size_t bytes = align256(st.op.size());
-    if (!held_.empty() && (held_.size() == kHeldMax || bytes_ + bytes > kRingSlotBytes)) {
+  int push(std::unique_ptr<Step> st) {
+    const size_t bytes = align256(st->op.size());
+    const bool early = first_ && std::holds_alternative<Lowered>(st->what) && bytes >= kRingSlotBytes / 4;
+    if (!held_.empty() && (held_.size() == kHeldMax || bytes_ + bytes > (early ? kRingSlotBytes / 2 : kRingSlotBytes))) {
       const int rc = flush();
       if (rc) return rc;
+      first_ = false;
     }
     bytes_ += bytes;
     held_.push_back(std::move(st));
@@ -587,15 +595,15 @@ class Runner {
     int slot = -1;
     if (bytes_) {
       std::vector<Part> parts;
-      for (const Step &st : held_) parts.push_back({st.op.data(), st.op.size()});
+      for (const auto &st : held_) parts.push_back({st->op.data(), st->op.size()});
       const int rc = stage(s_, parts, &dev, &slot);
       if (rc) return rc;
     }
     size_t at = 0;
-    for (const Step &st : held_) {
-      const int rc = launch_step(s_, st, static_cast<const char *>(dev) + at);
+    for (const auto &st : held_) {
+      const int rc = launch_step(s_, *st, static_cast<const char *>(dev) + at);
       if (rc) return rc;
-      at += align256(st.op.size());
+      at += align256(st->op.size());
     }
     held_.clear();
     bytes_ = 0;
@@ -605,8 +613,9 @@ class Runner {
  private:
   static constexpr size_t kHeldMax = 64;
   sv_state *s_;
-  std::vector<Step> held_;
+  std::vector<std::unique_ptr<Step>> held_;
   size_t bytes_ = 0;
+  bool first_ = true;
 };
 
 int run_list(sv_state *s, const std::vector<SeqGate> &gates);
@@ -623,11 +632,11 @@ int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
   const sv_stats before = s->stats;
   Runner run(s);
   for (pass::Step &x : q.steps) {
-    Step st;
+    std::unique_ptr<Step> st(new Step);
     if (x.pass.S > 0) {
-      pass_step(std::move(x.pass), &st);
+      pass_step(std::move(x.pass), st.get());
     } else {
-      const int rc = gate_step(s, q.items[size_t(x.items[0])], &st);
+      const int rc = gate_step(s, q.items[size_t(x.items[0])], st.get());
       if (rc) return rc;
     }
     const int rc = run.push(std::move(st));
@@ -660,19 +669,19 @@ int run_chains(sv_state *s, const std::vector<SeqGate> &gates) {
   const sv_stats before = s->stats;
   Runner run(s);
   for (chain::Step &x : chain::build(s->n, q.items)) {
-    Step st;
+    std::unique_ptr<Step> st(new Step);
     if (!x.fused) {
-      const int rc = gate_step(s, q.items[size_t(x.items[0])], &st);
+      const int rc = gate_step(s, q.items[size_t(x.items[0])], st.get());
       if (rc) return rc;
     } else {
       for (size_t g = 0; g < x.items.size(); ++g) {
         const pass::Item &y = q.items[size_t(x.items[g])];
-        const size_t at = st.op.size();
+        const size_t at = st->op.size();
         x.gate[g].op = int32_t(at);
-        st.op.resize(at + align256(mfma_operand_bytes(y.k, s->prec)));
-        pack_mfma_operand(y.k, s->prec, y.m, st.op.data() + at);
+        st->op.resize(at + align256(mfma_operand_bytes(y.k, s->prec)));
+        pack_mfma_operand(y.k, s->prec, y.m, st->op.data() + at);
       }
-      st.what = std::move(x);
+      st->what = std::move(x);
     }
     const int rc = run.push(std::move(st));
     if (rc) return rc;

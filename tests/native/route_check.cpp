@@ -3,6 +3,7 @@
 // copies for them, and what a failed launch leaves.  The argument names a check.
 #include "host_runtime.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -155,8 +156,30 @@ void packed_once() {
   }
 }
 
+// The device has work after two seven-qubit operands, whatever follows.
+void first_copy_early() {
+  for (int n : {8, 14, 24}) {
+    std::vector<Gate> gates;
+    for (int i = 0; i < 12; ++i) gates.push_back(dense(targets(n, 7)));
+    sv_state *s = state(n);
+    sv_plan *p = plan_of(n, gates);
+    rt::start();
+    CHECK(sv_run_plan(s, p) == SV_OK, "%s", sv_last_error());
+    rt::stop();
+    size_t copied = 0;
+    for (const rt::Event &e : rt::events()) {
+      if (!e.kernel.empty()) break;
+      copied += e.bytes;
+    }
+    CHECK(copied > 0 && copied <= size_t(2) << 17, "n=%d: %zu bytes before the first launch", n, copied);
+    sv_plan_free(p);
+    sv_free(s);
+  }
+}
+
 const std::map<std::string, std::function<void()>> kChecks = {
     {"packed_once", packed_once},
+    {"first_copy_early", first_copy_early},
 };
 
 }  // namespace
