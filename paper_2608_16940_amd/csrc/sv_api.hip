@@ -435,7 +435,6 @@ struct SeqGate {
 
 struct Sequence {
   std::vector<pass::Item> items;  // the gates that touch the state, on physical bits
-  std::vector<pass::Step> steps;
   int32_t Lend[64];               // the layout a run leaves
   sv_stats add;                   // the statistics a run adds, launches of single sweeps apart
 };
@@ -511,14 +510,13 @@ bool resolve_gate(int n, const SeqGate &g, int32_t *L, sv_stats *add, pass::Item
   return true;
 }
 
-// Resolves the gates from layout L on and cuts them into steps; every gate valid.
-void plan_sequence(const sv_state *s, const std::vector<SeqGate> &gates, const int32_t *L0, Sequence *q) {
+// Resolves the gates from the handle's layout on; every gate valid.
+void resolve(const sv_state *s, const std::vector<SeqGate> &gates, Sequence *q) {
   std::memset(&q->add, 0, sizeof(q->add));
-  std::memcpy(q->Lend, L0, sizeof(q->Lend));
+  std::memcpy(q->Lend, s->L, sizeof(q->Lend));
   pass::Item it;
   for (const SeqGate &g : gates)
     if (resolve_gate(s->n, g, q->Lend, &q->add, &it)) q->items.push_back(it);
-  q->steps = pass::build_steps(s->n, q->items, s->prec);
 }
 
 void finish_sequence(sv_state *s, const Sequence &q, const std::vector<SeqGate> &gates) {
@@ -628,10 +626,11 @@ int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
   for (const SeqGate &g : gates) narrow = narrow && (g.k == 1 || (g.k == 2 && is_diagonal(g.m, 2)));
   if (narrow) return run_list(s, gates);
   Sequence q;
-  plan_sequence(s, gates, s->L, &q);
+  resolve(s, gates, &q);
   const sv_stats before = s->stats;
   Runner run(s);
-  for (pass::Step &x : q.steps) {
+  pass::Cutter cut(s->n, q.items, s->prec);
+  for (pass::Step x; cut.next(&x);) {
     std::unique_ptr<Step> st(new Step);
     if (x.pass.S > 0) {
       pass_step(std::move(x.pass), st.get());
@@ -661,11 +660,7 @@ bool chainable(const sv_state *s) {
 // Runs valid gates in order as chains and single sweeps.
 int run_chains(sv_state *s, const std::vector<SeqGate> &gates) {
   Sequence q;
-  std::memset(&q.add, 0, sizeof(q.add));
-  std::memcpy(q.Lend, s->L, sizeof(q.Lend));
-  pass::Item it;
-  for (const SeqGate &g : gates)
-    if (resolve_gate(s->n, g, q.Lend, &q.add, &it)) q.items.push_back(it);
+  resolve(s, gates, &q);
   const sv_stats before = s->stats;
   Runner run(s);
   for (chain::Step &x : chain::build(s->n, q.items)) {
@@ -1317,9 +1312,10 @@ int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
   };
   if (fusible(s)) {
     Sequence q;
-    plan_sequence(s, gates, s->L, &q);
+    resolve(s, gates, &q);
     b->per_run = q.add;
-    for (pass::Step &x : q.steps) {
+    pass::Cutter cut(s->n, q.items, s->prec);
+    for (pass::Step x; cut.next(&x);) {
       Step st;
       if (x.pass.S > 0) {
         pass_step(std::move(x.pass), &st);

@@ -485,59 +485,75 @@ struct Builder {
 
 }  // namespace
 
-std::vector<Step> build_steps(int n, const std::vector<Item> &items, int prec) {
-  std::vector<Step> steps;
-  std::vector<char> done(items.size(), 0);
-  auto single = [&](int i) {
-    Step s;
-    s.items.push_back(i);
-    steps.push_back(std::move(s));
-  };
-  const Builder B(n, items, prec);
+struct Cutter::Draws {
+  const std::vector<Item> &items;
+  const Builder B;
+  std::vector<char> done;
+  size_t from = 0;
   // Dense gates of four bits or fewer with nothing else keep their own
   // sweeps: the layout swaps of sv_plan_swaps are priced by those, and a
   // sequence that gained the same from passes would make them a loss (20 + 20
   // alternating four-bit gates at N=30: 52 ms in passes with or without the
   // swap's 3 ms permutation; 117 and 98 ms in single sweeps).
   bool plain = true;
-  for (const Item &it : items) plain = plain && !it.diag && it.k <= 4;
-  size_t from = 0;
-  while (from < items.size()) {
-    if (done[from]) {
-      ++from;
-      continue;
+  std::vector<int> alone;  // drafted items that run by their own sweeps, the next one last
+
+  Draws(int n, const std::vector<Item> &it, int prec) : items(it), B(n, it, prec), done(it.size(), 0) {
+    for (const Item &x : it) plain = plain && !x.diag && x.k <= 4;
+  }
+
+  void single(int i, Step *s) {
+    s->items.assign(1, i);
+    s->pass = Fused();
+    done[size_t(i)] = 1;
+  }
+
+  bool next(Step *s) {
+    if (!alone.empty()) {
+      single(alone.back(), s);
+      alone.pop_back();
+      return true;
     }
-    const Item &it = items[from];
-    if (n < kMinS || plain || !B.takes(it)) {
-      single(int(from));
-      done[from] = 1;
-      continue;
+    while (from < items.size() && done[from]) ++from;
+    if (from == items.size()) return false;
+    if (B.n < kMinS || plain || !B.takes(items[from])) {
+      single(int(from), s);
+      return true;
     }
     Draft d = B.draft(done, from);
     B.trim(d, done);
+    if (d.items.empty()) {  // tables that cannot fit on their own
+      single(int(from), s);
+      return true;
+    }
     // one gate, or diagonals alone whose partial sweeps cost less than a pass
     // (on small states, where a launch of 3 us is all they cost, three of them
     // against the 9 us of a pass)
-    double alone = 0.0;
+    double cost = 0.0;
     int launches = 0;
     for (int i : d.items) {
-      alone += items[size_t(i)].sweep;
+      cost += items[size_t(i)].sweep;
       launches += items[size_t(i)].launches;
     }
-    Step s;
-    if (d.items.empty()) {  // tables that cannot fit on their own
-      single(int(from));
-      done[from] = 1;
-      continue;
-    }
+    s->pass = Fused();
     const bool lone = d.items.size() == 1 && items[size_t(d.items[0])].k != 6;
-    if (lone || (d.dense.empty() && (alone <= 1.1 || (n <= 18 && launches <= 3))) || !B.emit(d, &s.pass)) {
-      for (int i : d.items) single(i);
-      continue;
+    if (lone || (d.dense.empty() && (cost <= 1.1 || (B.n <= 18 && launches <= 3))) || !B.emit(d, &s->pass)) {
+      alone.assign(d.items.rbegin(), d.items.rend());
+      return next(s);
     }
-    s.items = d.items;
-    steps.push_back(std::move(s));
+    s->items = std::move(d.items);
+    return true;
   }
+};
+
+Cutter::Cutter(int n, const std::vector<Item> &items, int prec) : d_(new Draws(n, items, prec)) {}
+Cutter::~Cutter() { delete d_; }
+bool Cutter::next(Step *s) { return d_->next(s); }
+
+std::vector<Step> build_steps(int n, const std::vector<Item> &items, int prec) {
+  std::vector<Step> steps;
+  Cutter cut(n, items, prec);
+  for (Step s; cut.next(&s);) steps.push_back(std::move(s));
   return steps;
 }
 

@@ -88,8 +88,24 @@ struct Step {
 };
 
 // Cuts items into steps whose order is equivalent to the given one (gates
-// move only past gates on other bits, and diagonals past diagonals).
-// prec: SV_PREC_FP32 or SV_PREC_BF16X3.
+// move only past gates on other bits, and diagonals past diagonals), one step
+// at a time: a caller launches a step while the next one is drafted and packed,
+// and holds no more of them than it wants.  prec: SV_PREC_FP32 or
+// SV_PREC_BF16X3; items outlive the cutter.
+class Cutter {
+ public:
+  Cutter(int n, const std::vector<Item> &items, int prec);
+  ~Cutter();
+  Cutter(const Cutter &) = delete;
+  Cutter &operator=(const Cutter &) = delete;
+  bool next(Step *s);  // false when no step is left
+
+ private:
+  struct Draws;
+  Draws *const d_;
+};
+
+// All steps of a sequence.
 std::vector<Step> build_steps(int n, const std::vector<Item> &items, int prec);
 
 // Operands come in chunks of this size: a five-bit gate is one chunk (two

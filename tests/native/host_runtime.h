@@ -50,15 +50,14 @@ inline std::vector<std::string> launched() {
   return out;
 }
 
-// "k_name" from a mangled name
+// "k_name" from a mangled name: what follows it is upper case
 inline std::string short_name(const char *mangled) {
   const std::string s(mangled);
   const size_t at = s.find("k_");
   if (at == std::string::npos) return s;
-  size_t len = 0, p = at;
-  while (p > 0 && s[p - 1] >= '0' && s[p - 1] <= '9') --p;
-  for (size_t i = p; i < at; ++i) len = 10 * len + size_t(s[i] - '0');
-  return s.substr(at, len ? len : std::string::npos);
+  size_t end = at;
+  while (end < s.size() && (s[end] == '_' || (s[end] >= 'a' && s[end] <= 'z') || (s[end] >= '0' && s[end] <= '9'))) ++end;
+  return s.substr(at, end - at);
 }
 
 }  // namespace rt

@@ -177,8 +177,34 @@ void first_copy_early() {
   }
 }
 
+// A long plan is launched while it is cut: what is held of it stays bounded, and
+// the device does not wait for the whole plan.
+void long_plan_bounded() {
+  const int n = 30;
+  std::vector<Gate> gates;
+  for (int i = 0; i < 400; ++i) {
+    gates.push_back(dense(window(n, 6)));
+    gates.push_back(diagonal(targets(n, 2)));
+  }
+  sv_state *s = state(n);
+  sv_plan *p = plan_of(n, gates);
+  rt::start();
+  CHECK(sv_run_plan(s, p) == SV_OK, "%s", sv_last_error());
+  rt::stop();
+  size_t first = 0;
+  for (const rt::Event &e : rt::events())
+    if (!e.kernel.empty() && !first) first = e.allocated;
+  CHECK(count("k_pass") > 50, "%zu passes", count("k_pass"));
+  // a slot's worth of passes, the one being packed, 256 bytes a gate for the list
+  CHECK(rt::peak < (size_t(2) << 20) + 256 * gates.size(), "%zu bytes held", rt::peak);
+  CHECK(first < rt::allocated / 4, "first launch after %zu of %zu bytes", first, rt::allocated);
+  sv_plan_free(p);
+  sv_free(s);
+}
+
 const std::map<std::string, std::function<void()>> kChecks = {
     {"packed_once", packed_once},
+    {"long_plan_bounded", long_plan_bounded},
     {"first_copy_early", first_copy_early},
 };
 

@@ -33,7 +33,7 @@ def exe():
     return path
 
 
-@pytest.mark.parametrize("check", ["packed_once", "first_copy_early"])
+@pytest.mark.parametrize("check", ["packed_once", "first_copy_early", "long_plan_bounded"])
 def test_route(exe, check):
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, (r.stdout[-4000:], r.stderr[-2000:])
