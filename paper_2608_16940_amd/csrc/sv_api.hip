@@ -566,19 +566,28 @@ int launch_step(sv_state *s, const Step &st, const char *dev) {
 // Launches steps in order.  Operands of steps that follow each other are staged
 // by one copy, which costs some 15 us on the host and on the device.  Steps are
 // held until a slot is full; a step that no longer fits opens the next one.
-// Seven-qubit operands, which take longest to pack, start with two, so that the
-// device has work meanwhile (four such gates on 8 qubits from an idle stream:
-// 267 us held to a full slot, 182 in pairs; plans of five- and six-qubit gates
-// lose by an earlier copy, 154 to 175 us for two layers on a 10-qubit density
-// matrix).
+// Gates whose operands take long to pack are held less, so that the device has
+// work meanwhile:
+//   BF16x3, whose split takes ten times as long as FP32's packing, by 32 KiB
+//     (n=22, 12 layers in blocks of five from an idle stream: 2.00 ms by slots,
+//     1.68 so)
+//   seven qubits, starting with two (four of them on 8 qubits: 267 us by
+//     slots, 182 so; plans of five- and six-qubit gates lose by an earlier
+//     copy, 154 to 175 us for two layers on a 10-qubit density matrix).
 class Runner {
  public:
   explicit Runner(sv_state *s) : s_(s) {}
 
   int push(std::unique_ptr<Step> st) {
     const size_t bytes = align256(st->op.size());
-    const bool early = first_ && std::holds_alternative<Lowered>(st->what) && bytes >= kRingSlotBytes / 4;
-    if (!held_.empty() && (held_.size() == kHeldMax || bytes_ + bytes > (early ? kRingSlotBytes / 2 : kRingSlotBytes))) {
+    size_t most = kRingSlotBytes;
+    if (const Lowered *L = std::get_if<Lowered>(&st->what)) {
+      if (L->variant == SV_VARIANT_MFMA && s_->prec == SV_PREC_BF16X3)
+        most = kRingSlotBytes / 16;
+      else if (first_ && bytes >= kRingSlotBytes / 4)
+        most = kRingSlotBytes / 2;
+    }
+    if (!held_.empty() && (held_.size() == kHeldMax || bytes_ + bytes > most)) {
       const int rc = flush();
       if (rc) return rc;
       first_ = false;

@@ -175,6 +175,18 @@ void first_copy_early() {
     sv_plan_free(p);
     sv_free(s);
   }
+  // nor for more than four five-bit splits
+  std::vector<Gate> gates;
+  for (int i = 0; i < 40; ++i) gates.push_back(dense(targets(22, 5)));
+  sv_state *s = state(22);
+  sv_set_option(s, SV_OPT_PRECISION, SV_PREC_BF16X3);
+  sv_plan *p = plan_of(22, gates);
+  rt::start();
+  CHECK(sv_run_plan(s, p) == SV_OK, "%s", sv_last_error());
+  rt::stop();
+  for (const rt::Event &e : rt::events()) CHECK(e.bytes <= size_t(4) << 13, "%zu bytes in one copy", e.bytes);
+  sv_plan_free(p);
+  sv_free(s);
 }
 
 // A long plan is launched while it is cut: what is held of it stays bounded, and
