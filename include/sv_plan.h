@@ -181,7 +181,8 @@ int sv_plan_free(sv_plan *p);
  * be the one the plan was bound with, and leaves it as sv_run_plan would
  * (blocks that only permute qubits go to the layout map, as in
  * sv_apply_fused), so a second run needs a reset or the original layout.
- *   sv_bound_bytes      device bytes the operands need (*out; 0 if all by value)
+ *   sv_bound_bytes      device bytes that hold the operands (*out; 0 if all by
+ *                       value), the same for every layout of the handle
  *   sv_plan_bind        lower every block, copy the operands into op_dev
  *                       (caller-owned device memory, >= sv_bound_bytes,
  *                       256-B aligned; the copy completes before return)

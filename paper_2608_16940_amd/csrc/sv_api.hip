@@ -234,22 +234,26 @@ struct Lowered {
   std::vector<std::pair<int, int>> relabel;  // MFMA store-side bit exchanges
 };
 
-// Choose the kernel for a gate on physical targets A and prepare its
-// operands (the selector of the lowering step; Section IV-E).
-int lower(const sv_state *s, const double *matrix, const int32_t *A, int k, bool allow_relabel, Lowered *L) {
+// every off-diagonal entry exactly zero
+bool is_diagonal(const double *m, int k) {
+  const int D = 1 << k;
+  for (int r = 0; r < D; ++r)
+    for (int c = 0; c < D; ++c)
+      if (r != c && (m[2 * (r * D + c)] != 0.0 || m[2 * (r * D + c) + 1] != 0.0)) return false;
+  return true;
+}
+
+// Choose the kernel for a gate on physical targets A (the selector of the
+// lowering step; Section IV-E) and say how many bytes its operand takes in
+// device memory (0: by value).
+int select(const sv_state *s, const double *matrix, const int32_t *A, int k, int *variant, size_t *bytes) {
   const int n = s->n;
   int v = s->variant;
   const bool shuffle_ok = (k == 1 && A[0] <= 6);
   const bool mfma_ok = (k >= 4 && k <= 7 && n >= k + mfma_tile_M(k));
   const bool valu_ok = (k <= 4);
-  const int D = 1 << k;
-  bool diag = true;  // every off-diagonal entry exactly zero
-  for (int r = 0; r < D && diag; ++r)
-    for (int c = 0; c < D; ++c)
-      if (r != c && (matrix[2 * (r * D + c)] != 0.0 || matrix[2 * (r * D + c) + 1] != 0.0)) {
-        diag = false;
-        break;
-      }
+  const size_t D = size_t(1) << k;
+  const bool diag = is_diagonal(matrix, k);
   if (v == SV_VARIANT_AUTO) {
     if (diag)
       v = SV_VARIANT_DIAG;
@@ -262,6 +266,51 @@ int lower(const sv_state *s, const double *matrix, const int32_t *A, int k, bool
     else
       v = SV_VARIANT_GENERIC;
   }
+  *variant = v;
+  *bytes = 0;
+  switch (v) {
+    case SV_VARIANT_DIAG:
+      if (!diag) {
+        set_error("diagonal lowering needs a diagonal matrix");
+        return SV_ERR_UNSUPPORTED;
+      }
+      if (k > 4) *bytes = D * sizeof(float2);  // smaller tables ride in the kernel arguments
+      return SV_OK;
+    case SV_VARIANT_SHUFFLE:
+    case SV_VARIANT_VALU:
+      if ((v == SV_VARIANT_SHUFFLE && !shuffle_ok) || (v == SV_VARIANT_VALU && !valu_ok)) {
+        set_error("forced variant does not apply to this gate");
+        return SV_ERR_UNSUPPORTED;
+      }
+      return SV_OK;
+    case SV_VARIANT_MFMA:
+      if (!mfma_ok) {
+        set_error("MFMA lowering needs 4 <= k <= 7 and a state of at least k + tile bits");
+        return SV_ERR_UNSUPPORTED;
+      }
+      *bytes = mfma_operand_bytes(k, s->prec);
+      return SV_OK;
+    case SV_VARIANT_GENERIC:
+      if (k > 8) {
+        set_error("generic lowering supports k <= 8");
+        return SV_ERR_UNSUPPORTED;
+      }
+      *bytes = D * D * sizeof(float2);
+      return SV_OK;
+    default:
+      set_error("unknown variant");
+      return SV_ERR_ARG;
+  }
+}
+
+// Select the kernel for a gate and prepare its operands.
+int lower(const sv_state *s, const double *matrix, const int32_t *A, int k, bool allow_relabel, Lowered *L) {
+  const int n = s->n, D = 1 << k;
+  int v = 0;
+  size_t bytes = 0;
+  const int rc = select(s, matrix, A, k, &v, &bytes);
+  if (rc) return rc;
+  L->op.resize(bytes);
   L->variant = v;
   L->k = k;
   for (int j = 0; j < k; ++j) L->A[j] = A[j];
@@ -269,10 +318,6 @@ int lower(const sv_state *s, const double *matrix, const int32_t *A, int k, bool
   L->opsrc = s->opsrc;
   switch (v) {
     case SV_VARIANT_DIAG: {
-      if (!diag) {
-        set_error("diagonal lowering needs a diagonal matrix");
-        return SV_ERR_UNSUPPORTED;
-      }
       std::vector<float2> d(static_cast<size_t>(D));
       for (int r = 0; r < D; ++r)
         d[r] = make_float2(float(matrix[2 * (r * D + r)]), float(matrix[2 * (r * D + r) + 1]));
@@ -282,29 +327,19 @@ int lower(const sv_state *s, const double *matrix, const int32_t *A, int k, bool
         dd[2 * size_t(r) + 1] = matrix[2 * (r * D + r) + 1];
       }
       L->cover = diag_cover(k, dd.data(), A);
-      if (k <= 4) {  // small tables ride in the kernel arguments
-        L->by_value = true;
+      L->by_value = bytes == 0;
+      if (L->by_value)
         for (int r = 0; r < D; ++r) L->m[r] = d[r];
-      } else {
-        L->op.resize(d.size() * sizeof(float2));
-        std::memcpy(L->op.data(), d.data(), L->op.size());
-      }
+      else
+        std::memcpy(L->op.data(), d.data(), bytes);
       return SV_OK;
     }
     case SV_VARIANT_SHUFFLE:
     case SV_VARIANT_VALU:
-      if ((v == SV_VARIANT_SHUFFLE && !shuffle_ok) || (v == SV_VARIANT_VALU && !valu_ok)) {
-        set_error("forced variant does not apply to this gate");
-        return SV_ERR_UNSUPPORTED;
-      }
       L->by_value = true;
       for (int i = 0; i < D * D; ++i) L->m[i] = make_float2(float(matrix[2 * i]), float(matrix[2 * i + 1]));
       return SV_OK;
     case SV_VARIANT_MFMA: {
-      if (!mfma_ok) {
-        set_error("MFMA lowering needs 4 <= k <= 7 and a state of at least k + tile bits");
-        return SV_ERR_UNSUPPORTED;
-      }
       if (s->lazy && allow_relabel) L->relabel = plan_relabel(s, A, k, mfma_tile_M(k));
       uint64_t extra = 0;
       for (auto &pr : L->relabel) extra |= uint64_t(1) << pr.second;
@@ -325,24 +360,14 @@ int lower(const sv_state *s, const double *matrix, const int32_t *A, int k, bool
         L->tp.loc_out[ba] = L->tp.loc_out[bv];
         L->tp.loc_out[bv] = t;
       }
-      L->op.resize(mfma_operand_bytes(k, s->prec));
       pack_mfma_operand(k, s->prec, matrix, L->op.data());
       return SV_OK;
     }
-    case SV_VARIANT_GENERIC: {
-      if (k > 8) {
-        set_error("generic lowering supports k <= 8");
-        return SV_ERR_UNSUPPORTED;
-      }
-      std::vector<float2> m(size_t(D) * D);
-      for (size_t i = 0; i < m.size(); ++i) m[i] = make_float2(float(matrix[2 * i]), float(matrix[2 * i + 1]));
-      L->op.resize(m.size() * sizeof(float2));
-      std::memcpy(L->op.data(), m.data(), L->op.size());
+    default: {  // SV_VARIANT_GENERIC
+      float2 *m = reinterpret_cast<float2 *>(L->op.data());
+      for (int i = 0; i < D * D; ++i) m[i] = make_float2(float(matrix[2 * i]), float(matrix[2 * i + 1]));
       return SV_OK;
     }
-    default:
-      set_error("unknown variant");
-      return SV_ERR_ARG;
   }
 }
 
@@ -446,14 +471,6 @@ bool valid_targets(int n, const int32_t *t, int k) {
     for (int i = 0; i < j; ++i)
       if (t[i] == t[j]) return false;
   }
-  return true;
-}
-
-bool is_diagonal(const double *m, int k) {
-  const int D = 1 << k;
-  for (int r = 0; r < D; ++r)
-    for (int c = 0; c < D; ++c)
-      if (r != c && (m[2 * (r * D + c)] != 0.0 || m[2 * (r * D + c) + 1] != 0.0)) return false;
   return true;
 }
 
@@ -1286,16 +1303,12 @@ struct sv_bound {
 
 namespace {
 
-int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
+// The gates of a plan that can be bound to s.
+int bindable_gates(const sv_state *s, const sv_plan *p, std::vector<SeqGate> *gates) {
   if (s->lazy) {
     set_error("bound plans need lazy relabel off");
     return SV_ERR_ARG;
   }
-  b->s = s;
-  std::memcpy(b->L, s->L, sizeof(b->L));
-  std::memcpy(b->Lend, s->L, sizeof(b->Lend));
-  std::memset(&b->per_run, 0, sizeof(b->per_run));
-  std::vector<SeqGate> gates;
   for (const SvBlock &k : p->blocks) {
     if (k.swap) {
       set_error("a plan with layout-swap blocks runs through sv_run_plan, not as a bound plan");
@@ -1305,8 +1318,47 @@ int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
       set_error("plan target outside the state");
       return SV_ERR_ARG;
     }
-    gates.push_back({k.matrix.data(), k.tuple.data(), k.k});
+    gates->push_back({k.matrix.data(), k.tuple.data(), k.k});
   }
+  return SV_OK;
+}
+
+// Operand bytes of a bound plan, at most: the larger of a gate's own operand
+// and its share of a pass, gate by gate.  Nothing is cut or packed for it, and
+// it is the same for every layout, so a buffer of this size serves a plan that
+// is bound again after a run has moved the layout.
+int bound_bytes(const sv_state *s, const sv_plan *p, size_t *bytes) {
+  std::vector<SeqGate> gates;
+  int rc = bindable_gates(s, p, &gates);
+  if (rc) return rc;
+  const bool fuse = fusible(s);
+  int32_t L[64];
+  std::memcpy(L, s->L, sizeof(L));
+  *bytes = 0;
+  for (const SeqGate &g : gates) {
+    int32_t A[SV_MAX_K];
+    for (int j = 0; j < g.k; ++j) A[j] = L[g.t[j]];
+    int perm[SV_MAX_K], v = 0;
+    if (s->variant == SV_VARIANT_AUTO && qubit_permutation(g.m, g.k, perm)) {
+      for (int j = 0; j < g.k; ++j) L[g.t[perm[j]]] = A[j];
+      continue;
+    }
+    size_t own = 0;
+    rc = select(s, g.m, A, g.k, &v, &own);
+    if (rc) return rc;
+    *bytes += align256(std::max(own, fuse ? pass::share_bytes(s->n, g.k, v == SV_VARIANT_DIAG, s->prec) : 0));
+  }
+  return SV_OK;
+}
+
+int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
+  std::vector<SeqGate> gates;
+  const int ok = bindable_gates(s, p, &gates);
+  if (ok) return ok;
+  b->s = s;
+  std::memcpy(b->L, s->L, sizeof(b->L));
+  std::memcpy(b->Lend, s->L, sizeof(b->Lend));
+  std::memset(&b->per_run, 0, sizeof(b->per_run));
   size_t total = 0;
   auto add = [&](Step &&st) {
     BoundStep x;
@@ -1472,8 +1524,7 @@ int sv_bound_bytes(sv_state *s, const sv_plan *p, size_t *out) {
       set_error("null pointer");
       return SV_ERR_ARG;
     }
-    sv_bound b;
-    return lower_plan(s, p, &b, out);
+    return bound_bytes(s, p, out);
   });
 }
 

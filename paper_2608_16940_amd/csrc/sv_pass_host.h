@@ -8,6 +8,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "sv.h"
+
 namespace sv {
 namespace pass {
 
@@ -112,6 +114,17 @@ std::vector<Step> build_steps(int n, const std::vector<Item> &items, int prec);
 // reduction steps of 16), a six-bit gate four (one step each, two row tiles).
 constexpr size_t kChunkBytes = 6 * 2048;
 inline int chunks_of(int k) { return k == 6 ? 4 : 1; }
+
+// Bytes of device data a gate on k of n qubits adds to the passes of a
+// sequence, at most: what it brings itself, and a pass that it is alone in (the
+// head, a block that is always there, and the gaps to multiples of 256 bytes).
+inline size_t share_bytes(int n, int k, bool diag, int prec) {
+  if (n < kMinS || (!diag && (k > kGateBits || prec != SV_PREC_FP32))) return 0;
+  const size_t pass = sizeof(DevHead) + sizeof(DevBlk) + 8 * kTabBlock + 3 * 256;
+  if (!diag) return pass + sizeof(DevOp) + kChunkBytes * size_t(chunks_of(k));
+  return pass + sizeof(DevTab) + sizeof(DevBlk) * (size_t(1) << kTabInBits) / kTabBlock +
+         8 * ((size_t(1) << kTabBits) + kTabBlock);
+}
 
 }  // namespace pass
 }  // namespace sv
