@@ -187,7 +187,8 @@ int sv_plan_free(sv_plan *p);
  *                       (caller-owned device memory, >= sv_bound_bytes,
  *                       256-B aligned; the copy completes before return)
  *   sv_bound_run        launch every block (asynchronous), cut into the passes
- *                       sv_run_plan would run
+ *                       sv_run_plan would run, with the same bits (on a density
+ *                       handle block by block, with the same bits too)
  *   sv_bound_graph_run  first call: capture the launches into a HIP graph on
  *                       the handle's stream and instantiate it; every call:
  *                       launch the graph (asynchronous).  The graph holds

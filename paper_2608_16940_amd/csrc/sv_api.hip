@@ -458,12 +458,6 @@ struct SeqGate {
   int k;
 };
 
-struct Sequence {
-  std::vector<pass::Item> items;  // the gates that touch the state, on physical bits
-  int32_t Lend[64];               // the layout a run leaves
-  sv_stats add;                   // the statistics a run adds, launches of single sweeps apart
-};
-
 bool valid_targets(int n, const int32_t *t, int k) {
   if (k < 1 || k > n || k > SV_MAX_K) return false;
   for (int j = 0; j < k; ++j) {
@@ -527,19 +521,10 @@ bool resolve_gate(int n, const SeqGate &g, int32_t *L, sv_stats *add, pass::Item
   return true;
 }
 
-// Resolves the gates from the handle's layout on; every gate valid.
-void resolve(const sv_state *s, const std::vector<SeqGate> &gates, Sequence *q) {
-  std::memset(&q->add, 0, sizeof(q->add));
-  std::memcpy(q->Lend, s->L, sizeof(q->Lend));
-  pass::Item it;
-  for (const SeqGate &g : gates)
-    if (resolve_gate(s->n, g, q->Lend, &q->add, &it)) q->items.push_back(it);
-}
-
-void finish_sequence(sv_state *s, const Sequence &q, const std::vector<SeqGate> &gates) {
+void finish_sequence(sv_state *s, const int32_t *Lend, const std::vector<SeqGate> &gates) {
   for (int i = 0; i < s->n; ++i) {
-    s->L[i] = q.Lend[i];
-    s->Linv[q.Lend[i]] = i;
+    s->L[i] = Lend[i];
+    s->Linv[Lend[i]] = i;
   }
   for (const SeqGate &g : gates) {
     ++s->clock;
@@ -548,30 +533,127 @@ void finish_sequence(sv_state *s, const Sequence &q, const std::vector<SeqGate> 
 }
 
 // One launch of a sequence (a diagonal gate's few): a gate's own sweep, a fused
-// pass or a gate chain, and the operand it reads in device memory.
+// pass, a gate chain or a program, and the operand it reads in device memory.
 struct Step {
-  std::variant<Lowered, pass::Fused, chain::Step> what;
+  std::variant<Lowered, pass::Fused, chain::Step, std::unique_ptr<prog::Args>> what;
   std::vector<char> op;
 };
 
-int gate_step(const sv_state *s, const pass::Item &it, Step *st) {
-  Lowered &L = st->what.emplace<Lowered>();
-  const int rc = lower(s, it.m, it.A, it.k, false, &L);
-  st->op = std::move(L.op);
-  return rc;
+// Density handles: a plan's gates keep the arithmetic of their own sweeps bit
+// for bit, so they share passes as chains (sv_chain_host.h).
+bool chainable(const sv_state *s) {
+  return s->dm_n != 0 && s->variant == SV_VARIANT_AUTO && !s->lazy && s->mfma_min_k == 4 &&
+         s->opsrc == SV_MFMA_OPERAND_AUTO && s->tile_order == -1 && s->prec == SV_PREC_FP32;
 }
 
-void pass_step(pass::Fused &&f, Step *st) {
-  st->op = std::move(f.data);
-  st->what = std::move(f);
+// Sequences of narrow gates alone (an unfused circuit as a plan) run as
+// programs: a one-qubit gate in a pass of matrix-core gates acts as a five-qubit one.
+bool narrow(const sv_state *s, const std::vector<SeqGate> &gates) {
+  if (s->n < prog::kMinQubits) return false;
+  for (const SeqGate &g : gates)
+    if (g.k != 1 && !(g.k == 2 && is_diagonal(g.m, 2))) return false;
+  return true;
 }
+
+// The steps of a sequence of valid gates known in full, from the handle's layout
+// on: what a plan runs as on a fusible or chainable handle, and what a bound plan
+// holds on a fusible one.  Passes are cut and operands packed as the steps are asked for.
+class Steps {
+ public:
+  Steps(const sv_state *s, const std::vector<SeqGate> &gates) : s_(s) {
+    std::memset(&add, 0, sizeof(add));
+    std::memcpy(Lend, s->L, sizeof(Lend));
+    pass::Item it;
+    for (const SeqGate &g : gates)
+      if (resolve_gate(s->n, g, Lend, &add, &it)) items_.push_back(it);
+    if (chainable(s))
+      chains_ = chain::build(s->n, items_);
+    else if (narrow(s, gates))
+      prog::build(s->n, items_, &programs_);
+    else
+      cut_.reset(new pass::Cutter(s->n, items_, s->prec));
+  }
+
+  // The next step, or null after the last.
+  int next(std::unique_ptr<Step> *out) {
+    out->reset();
+    if (!singles_.empty()) return single(out);
+    std::unique_ptr<Step> st;
+    if (cut_) {
+      pass::Step x;
+      if (!cut_->next(&x)) return SV_OK;
+      if (x.pass.S == 0) {
+        singles_ = x.items;
+        return single(out);
+      }
+      st.reset(new Step);
+      st->op = std::move(x.pass.data);
+      st->what = std::move(x.pass);
+    } else if (at_ < chains_.size()) {
+      chain::Step &x = chains_[at_++];
+      if (!x.fused) {
+        singles_ = x.items;
+        return single(out);
+      }
+      st.reset(new Step);
+      for (size_t g = 0; g < x.items.size(); ++g) {
+        const pass::Item &y = items_[size_t(x.items[g])];
+        const size_t at = st->op.size();
+        x.gate[g].op = int32_t(at);
+        st->op.resize(at + align256(mfma_operand_bytes(y.k, s_->prec)));
+        pack_mfma_operand(y.k, s_->prec, y.m, st->op.data() + at);
+      }
+      st->what = std::move(x);
+    } else if (at_ < programs_.size()) {
+      prog::Step &x = programs_[at_++];
+      if (!x.fused) {
+        singles_.assign(x.items.rbegin(), x.items.rend());
+        return single(out);
+      }
+      st.reset(new Step);
+      st->what.emplace<std::unique_ptr<prog::Args>>(new prog::Args(x.args));
+    } else {
+      return SV_OK;
+    }
+    *out = std::move(st);
+    return SV_OK;
+  }
+
+  int32_t Lend[64];  // the layout a run leaves
+  sv_stats add;      // the statistics a run adds, launches apart
+
+ private:
+  int single(std::unique_ptr<Step> *out) {  // the last of singles_ by its own sweep
+    const pass::Item &it = items_[size_t(singles_.back())];
+    singles_.pop_back();
+    std::unique_ptr<Step> st(new Step);
+    Lowered &L = st->what.emplace<Lowered>();
+    const int rc = lower(s_, it.m, it.A, it.k, false, &L);
+    if (rc) return rc;
+    st->op = std::move(L.op);
+    *out = std::move(st);
+    return SV_OK;
+  }
+
+  const sv_state *s_;
+  std::vector<pass::Item> items_;  // the gates that touch the state, on physical bits
+  std::vector<chain::Step> chains_;
+  std::vector<prog::Step> programs_;
+  std::unique_ptr<pass::Cutter> cut_;
+  std::vector<int> singles_;
+  size_t at_ = 0;
+};
 
 // dev: the step's operand in device memory.
 int launch_step(sv_state *s, const Step &st, const char *dev) {
   if (const Lowered *L = std::get_if<Lowered>(&st.what)) return launch_lowered(s, *L, dev);
-  const pass::Fused *f = std::get_if<pass::Fused>(&st.what);
-  const hipError_t e = f ? pass::launch(s->n, *f, s->amps, dev, s->st)
-                         : chain::launch(s->n, std::get<chain::Step>(st.what), s->amps, dev, s->st);
+  hipError_t e;
+  if (const pass::Fused *f = std::get_if<pass::Fused>(&st.what))
+    e = pass::launch(s->n, *f, s->amps, dev, s->st);
+  else if (const chain::Step *c = std::get_if<chain::Step>(&st.what))
+    e = chain::launch(s->n, *c, s->amps, dev, s->st);
+  else
+    e = prog::launch(*std::get<std::unique_ptr<prog::Args>>(st.what), s->amps, s->st);
   if (e != hipSuccess) {
     set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
     return SV_ERR_DEVICE;
@@ -642,77 +724,24 @@ class Runner {
   bool first_ = true;
 };
 
-int run_list(sv_state *s, const std::vector<SeqGate> &gates);
-
-// Runs valid gates in order through fused passes.  Sequences of narrow gates
-// alone (an unfused circuit as a plan) run as programs: a one-qubit gate in a
-// pass of matrix-core gates acts as a five-qubit one.
-int run_gates(sv_state *s, const std::vector<SeqGate> &gates) {
-  bool narrow = s->n >= prog::kMinQubits;
-  for (const SeqGate &g : gates) narrow = narrow && (g.k == 1 || (g.k == 2 && is_diagonal(g.m, 2)));
-  if (narrow) return run_list(s, gates);
-  Sequence q;
-  resolve(s, gates, &q);
+// Runs a sequence of valid gates.
+int run_steps(sv_state *s, const std::vector<SeqGate> &gates) {
   const sv_stats before = s->stats;
+  Steps steps(s, gates);
   Runner run(s);
-  pass::Cutter cut(s->n, q.items, s->prec);
-  for (pass::Step x; cut.next(&x);) {
-    std::unique_ptr<Step> st(new Step);
-    if (x.pass.S > 0) {
-      pass_step(std::move(x.pass), st.get());
-    } else {
-      const int rc = gate_step(s, q.items[size_t(x.items[0])], st.get());
-      if (rc) return rc;
-    }
-    const int rc = run.push(std::move(st));
+  for (std::unique_ptr<Step> st;;) {
+    int rc = steps.next(&st);
+    if (rc) return rc;
+    if (!st) break;
+    rc = run.push(std::move(st));
     if (rc) return rc;
   }
   const int rc = run.flush();
   if (rc) return rc;
-  q.add.launches = s->stats.launches - before.launches;
+  steps.add.launches = s->stats.launches - before.launches;
   s->stats = before;
-  add_stats(&s->stats, q.add);
-  finish_sequence(s, q, gates);
-  return SV_OK;
-}
-
-// Density handles: a plan's gates keep the arithmetic of their own sweeps bit
-// for bit, so they share passes as chains (sv_chain_host.h).
-bool chainable(const sv_state *s) {
-  return s->dm_n != 0 && s->variant == SV_VARIANT_AUTO && !s->lazy && s->mfma_min_k == 4 &&
-         s->opsrc == SV_MFMA_OPERAND_AUTO && s->tile_order == -1 && s->prec == SV_PREC_FP32;
-}
-
-// Runs valid gates in order as chains and single sweeps.
-int run_chains(sv_state *s, const std::vector<SeqGate> &gates) {
-  Sequence q;
-  resolve(s, gates, &q);
-  const sv_stats before = s->stats;
-  Runner run(s);
-  for (chain::Step &x : chain::build(s->n, q.items)) {
-    std::unique_ptr<Step> st(new Step);
-    if (!x.fused) {
-      const int rc = gate_step(s, q.items[size_t(x.items[0])], st.get());
-      if (rc) return rc;
-    } else {
-      for (size_t g = 0; g < x.items.size(); ++g) {
-        const pass::Item &y = q.items[size_t(x.items[g])];
-        const size_t at = st->op.size();
-        x.gate[g].op = int32_t(at);
-        st->op.resize(at + align256(mfma_operand_bytes(y.k, s->prec)));
-        pack_mfma_operand(y.k, s->prec, y.m, st->op.data() + at);
-      }
-      st->what = std::move(x);
-    }
-    const int rc = run.push(std::move(st));
-    if (rc) return rc;
-  }
-  const int rc = run.flush();
-  if (rc) return rc;
-  q.add.launches = s->stats.launches - before.launches;
-  s->stats = before;
-  add_stats(&s->stats, q.add);
-  finish_sequence(s, q, gates);
+  add_stats(&s->stats, steps.add);
+  finish_sequence(s, steps.Lend, gates);
   return SV_OK;
 }
 
@@ -1285,7 +1314,7 @@ int sv_get_stats(const sv_state *s, sv_stats *out) {
 
 // ------------------------------------------------------------------ bound plans
 struct BoundStep {
-  Step step;
+  std::unique_ptr<Step> step;
   size_t off = SIZE_MAX;  // operand offset in op_dev (SIZE_MAX: by value)
 };
 
@@ -1331,10 +1360,11 @@ int bound_bytes(const sv_state *s, const sv_plan *p, size_t *bytes) {
   std::vector<SeqGate> gates;
   int rc = bindable_gates(s, p, &gates);
   if (rc) return rc;
+  *bytes = 0;
   const bool fuse = fusible(s);
+  if (fuse && narrow(s, gates)) return SV_OK;  // programs travel as kernel arguments
   int32_t L[64];
   std::memcpy(L, s->L, sizeof(L));
-  *bytes = 0;
   for (const SeqGate &g : gates) {
     int32_t A[SV_MAX_K];
     for (int j = 0; j < g.k; ++j) A[j] = L[g.t[j]];
@@ -1360,49 +1390,46 @@ int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
   std::memcpy(b->Lend, s->L, sizeof(b->Lend));
   std::memset(&b->per_run, 0, sizeof(b->per_run));
   size_t total = 0;
-  auto add = [&](Step &&st) {
+  auto add = [&](std::unique_ptr<Step> st) {
     BoundStep x;
-    x.step = std::move(st);
-    if (!x.step.op.empty()) {
+    if (!st->op.empty()) {
       x.off = total;
-      total += align256(x.step.op.size());
+      total += align256(st->op.size());
     }
-    const Lowered *L = std::get_if<Lowered>(&x.step.what);
+    const Lowered *L = std::get_if<Lowered>(&st->what);
     b->per_run.launches += L && L->variant == SV_VARIANT_DIAG ? L->cover.nsub : 1;
+    x.step = std::move(st);
     b->steps.push_back(std::move(x));
   };
+  // As sv_run_plan.  A density handle's gates keep their own sweeps, whose bits a
+  // chain's are: a graph has no launches to save, and chains of six-qubit gates
+  // are slower until the state leaves the caches (two noisy layers replayed:
+  // 89 us in sweeps and 110 in chains at 18 vector qubits, 135 and 145 at 20).
   if (fusible(s)) {
-    Sequence q;
-    resolve(s, gates, &q);
-    b->per_run = q.add;
-    pass::Cutter cut(s->n, q.items, s->prec);
-    for (pass::Step x; cut.next(&x);) {
-      Step st;
-      if (x.pass.S > 0) {
-        pass_step(std::move(x.pass), &st);
-      } else {
-        const int rc = gate_step(s, q.items[size_t(x.items[0])], &st);
-        if (rc) return rc;
-      }
+    Steps steps(s, gates);
+    b->per_run = steps.add;
+    for (std::unique_ptr<Step> st;;) {
+      const int rc = steps.next(&st);
+      if (rc) return rc;
+      if (!st) break;
       add(std::move(st));
     }
-    std::memcpy(b->Lend, q.Lend, sizeof(b->Lend));
+    std::memcpy(b->Lend, steps.Lend, sizeof(b->Lend));
   } else {
-    pass::Item it;
     for (const SeqGate &g : gates) {
-      it.k = g.k;
-      it.m = g.m;
-      for (int j = 0; j < g.k; ++j) it.A[j] = b->Lend[g.t[j]];
+      int32_t A[SV_MAX_K];
+      for (int j = 0; j < g.k; ++j) A[j] = b->Lend[g.t[j]];
       int perm[SV_MAX_K];
       if (s->variant == SV_VARIANT_AUTO && qubit_permutation(g.m, g.k, perm)) {  // as sv_apply_fused
-        for (int j = 0; j < g.k; ++j) b->Lend[g.t[perm[j]]] = it.A[j];
+        for (int j = 0; j < g.k; ++j) b->Lend[g.t[perm[j]]] = A[j];
         b->per_run.layout_only += 1;
         continue;
       }
-      Step st;
-      const int rc = gate_step(s, it, &st);
+      std::unique_ptr<Step> st(new Step);
+      Lowered &L = st->what.emplace<Lowered>();
+      const int rc = lower(s, g.m, A, g.k, false, &L);
       if (rc) return rc;
-      const Lowered &L = std::get<Lowered>(st.what);
+      st->op = std::move(L.op);
       b->per_run.gate_sweeps += 1;
       if (L.variant < 6) b->per_run.by_variant[L.variant] += 1;
       if (L.variant == SV_VARIANT_DIAG) b->per_run.diag_chunks += diag_chunks(L, s->n);
@@ -1428,7 +1455,7 @@ int bound_check(const sv_bound *b) {
 int bound_launch_all(sv_bound *b) {
   for (const BoundStep &st : b->steps) {
     const char *dev = st.off == SIZE_MAX ? nullptr : b->op_dev + st.off;
-    const int rc = launch_step(b->s, st.step, dev);
+    const int rc = launch_step(b->s, *st.step, dev);
     if (rc) return rc;
   }
   return SV_OK;
@@ -1458,7 +1485,7 @@ int sv_run_plan(sv_state *s, const sv_plan *p) {
     const size_t nb = p->blocks.size(), nq = size_t(std::max(p->n, s->n));
     std::vector<int64_t> next(nq, INT64_MAX);
     std::vector<std::vector<int64_t>> hints(nb);
-    const bool chains = chainable(s), fuse = fusible(s) || chains;
+    const bool fuse = fusible(s) || chainable(s);
     for (size_t i = nb; i-- > 0;) {
       // a fused run leaves the hints of its last block
       if (!fuse || i + 1 == nb || p->blocks[i + 1].swap) hints[i] = next;
@@ -1501,7 +1528,7 @@ int sv_run_plan(sv_state *s, const sv_plan *p) {
           rc = sv_hint_next_use(s, hints[j - 1].data());
           if (rc) return rc;
         }
-        rc = chains ? run_chains(s, gates) : run_gates(s, gates);
+        rc = run_steps(s, gates);
         if (rc) return rc;
         i = j;
         continue;
@@ -1546,7 +1573,7 @@ int sv_plan_bind(sv_state *s, const sv_plan *p, void *op_dev, size_t op_bytes, s
     std::vector<char> host(need);
     for (BoundStep &st : b->steps) {
       if (st.off == SIZE_MAX) continue;
-      std::vector<char> &src = st.step.op;
+      std::vector<char> &src = st.step->op;
       std::memcpy(host.data() + st.off, src.data(), src.size());
       src.clear();
       src.shrink_to_fit();

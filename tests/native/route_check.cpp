@@ -253,9 +253,76 @@ void bound_bytes_cheap_and_enough() {
       }
 }
 
+// A bound plan launches the kernels that the plan launches (on a density handle
+// each block's own), counts the same and leaves the same layout, also after the
+// plan is gone.
+void bound_runs_what_the_plan_runs() {
+  struct Handle {
+    int n, most, prec;
+    bool density;
+  };
+  const std::vector<Handle> handles = {
+      {3, 1, SV_PREC_FP32, false},  {4, 1, SV_PREC_FP32, false},   {12, 1, SV_PREC_FP32, false}, {23, 1, SV_PREC_FP32, false},
+      {26, 1, SV_PREC_FP32, false}, {12, 1, SV_PREC_BF16X3, false}, {9, 6, SV_PREC_FP32, false},  {10, 4, SV_PREC_FP32, false},
+      {16, 6, SV_PREC_FP32, false}, {24, 8, SV_PREC_FP32, false},  {16, 6, SV_PREC_BF16X3, false}, {6, 6, SV_PREC_FP32, true},
+      {9, 6, SV_PREC_FP32, true},   {12, 6, SV_PREC_FP32, true},   {10, 6, SV_PREC_BF16X3, true}};
+  for (const Handle &h : handles) {
+    const int n = h.density ? 2 * h.n : h.n;
+    std::vector<Gate> gates;
+    if (h.most == 1) {  // narrow ones: the sequence runs as programs
+      for (int i = 0; i < 120; ++i)
+        gates.push_back(i % 3 ? dense(targets(n, 1)) : diagonal(targets(n, 2)));
+    } else {
+      gates = mixed(n, h.most, 80);
+    }
+    sv_plan *p = plan_of(n, gates);
+    auto open = [&]() {
+      sv_state *s = nullptr;
+      const int rc = h.density ? sv_dm_alloc(&s, h.n, kAmps, sv_dm_state_bytes(h.n), kWork, sv_dm_workspace_bytes(h.n), nullptr)
+                               : sv_alloc(&s, n, kAmps, size_t(8) << n, kWork, sv_workspace_bytes(n), nullptr);
+      CHECK(rc == SV_OK, "%s", sv_last_error());
+      sv_set_option(s, SV_OPT_PRECISION, h.prec);
+      return s;
+    };
+    sv_state *a = open(), *b = open();
+    rt::start();
+    CHECK(sv_run_plan(a, p) == SV_OK, "%s", sv_last_error());
+    rt::stop();
+    const std::vector<std::string> want = rt::launched();
+    size_t need = 0;
+    sv_bound *bound = nullptr;
+    CHECK(sv_bound_bytes(b, p, &need) == SV_OK, "%s", sv_last_error());
+    CHECK(sv_plan_bind(b, p, kOps, need, &bound) == SV_OK, "%s", sv_last_error());
+    sv_plan_free(p);
+    rt::start();
+    CHECK(sv_bound_run(bound) == SV_OK, "%s", sv_last_error());
+    rt::stop();
+    const std::vector<std::string> ran = rt::launched();
+    CHECK(h.density ? count("k_chain") == 0 && ran.size() >= want.size() : ran == want,
+          "n=%d k<=%d prec=%d density=%d: %zu launches bound, %zu as a plan", n, h.most, h.prec, int(h.density), ran.size(),
+          want.size());
+    CHECK(layout(a, n) == layout(b, n), "n=%d: layouts differ", n);
+    sv_stats x, y;
+    sv_get_stats(a, &x);
+    sv_get_stats(b, &y);
+    if (h.density) y.launches = x.launches;
+    CHECK(std::memcmp(&x, &y, sizeof(x)) == 0, "n=%d k<=%d density=%d: statistics differ", n, h.most, int(h.density));
+    // the graph's kernels are the same ones
+    sv_reset(b);
+    rt::start();
+    CHECK(sv_bound_graph_run(bound) == SV_OK, "%s", sv_last_error());
+    rt::stop();
+    CHECK(rt::launched() == ran, "n=%d k<=%d: %zu launches captured", n, h.most, rt::launched().size());
+    sv_bound_free(bound);
+    sv_free(a);
+    sv_free(b);
+  }
+}
+
 const std::map<std::string, std::function<void()>> kChecks = {
     {"packed_once", packed_once},
     {"bound_bytes_cheap_and_enough", bound_bytes_cheap_and_enough},
+    {"bound_runs_what_the_plan_runs", bound_runs_what_the_plan_runs},
     {"long_plan_bounded", long_plan_bounded},
     {"first_copy_early", first_copy_early},
 };
