@@ -1,6 +1,7 @@
 """Bound plans of every route against plan.run: the same bits, also replayed as a graph."""
 import numpy as np
 import pytest
+import torch  # noqa: F401  the library shares its HIP runtime: loaded first
 
 from workloads import circuits as C
 
