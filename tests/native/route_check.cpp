@@ -319,10 +319,36 @@ void bound_runs_what_the_plan_runs() {
   }
 }
 
+// Narrow gates in passes are packed from their own entries, not from a padded matrix.
+void narrow_gates_packed_lean() {
+  const int n = 20;
+  for (int k : {1, 2, 3}) {
+    std::vector<Gate> gates;
+    for (int i = 0; i < 60; ++i) gates.push_back(dense(window(n, k)));
+    for (int i = 0; i < 20; ++i) gates.push_back(diagonal(window(n, 5)));
+    sv_state *s = state(n);
+    sv_plan *p = plan_of(n, gates);
+    size_t need = 0;
+    CHECK(sv_bound_bytes(s, p, &need) == SV_OK, "%s", sv_last_error());
+    sv_bound *b = nullptr;
+    rt::start();
+    CHECK(sv_plan_bind(s, p, kOps, need, &b) == SV_OK, "%s", sv_last_error());
+    rt::stop();
+    size_t copied = 0;
+    for (const rt::Event &e : rt::events()) copied += e.bytes;
+    // the steps' operands and the copy that is uploaded, and 6 KiB a gate for descriptors and drafts
+    CHECK(rt::allocated < 2 * copied + 6144 * gates.size(), "k=%d: %zu allocated for %zu", k, rt::allocated, copied);
+    sv_bound_free(b);
+    sv_plan_free(p);
+    sv_free(s);
+  }
+}
+
 const std::map<std::string, std::function<void()>> kChecks = {
     {"packed_once", packed_once},
     {"bound_bytes_cheap_and_enough", bound_bytes_cheap_and_enough},
     {"bound_runs_what_the_plan_runs", bound_runs_what_the_plan_runs},
+    {"narrow_gates_packed_lean", narrow_gates_packed_lean},
     {"long_plan_bounded", long_plan_bounded},
     {"first_copy_early", first_copy_early},
 };
