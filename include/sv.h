@@ -100,7 +100,9 @@ int sv_apply_fused(sv_state *s, const double *matrix, const int32_t *targets, in
  *   ks        count gate widths
  *   targets   the gates' targets one after the other
  *   matrices  the gates' matrices one after the other; copied before return
- * Errors: as sv_apply_fused.
+ * Errors: as sv_apply_fused.  After SV_ERR_DEVICE the layout and statistics are
+ * those of the gates that ran, but gates that were to share a pass with the
+ * failing one may have acted on the state in part.
  */
 int sv_apply_gates(sv_state *s, int64_t count, const int32_t *ks, const int32_t *targets, const double *matrices);
 

@@ -166,7 +166,10 @@ int sv_plan_block_swap(const sv_plan *p, int i, int *is_swap, int32_t *dest);
  * several to a pass over the state (FP32: dense blocks of up to 6 qubits and
  * diagonal ones; BF16x3: diagonal blocks of entries 1, -1, i, -i), blocks on
  * different qubits in either order; statistics count blocks as before, and
- * launches the kernels that ran. */
+ * launches the kernels that ran.  After SV_ERR_DEVICE the amplitudes are
+ * undefined: some blocks between two layout swaps have run, not always the
+ * first ones, and layout and statistics do not count them; sv_reset makes the
+ * handle usable again. */
 int sv_run_plan(sv_state *s, const sv_plan *p);
 
 int sv_plan_free(sv_plan *p);

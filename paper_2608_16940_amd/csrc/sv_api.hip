@@ -521,16 +521,36 @@ bool resolve_gate(int n, const SeqGate &g, int32_t *L, sv_stats *add, pass::Item
   return true;
 }
 
-void finish_sequence(sv_state *s, const int32_t *Lend, const std::vector<SeqGate> &gates) {
+// Records that gates [g, end) have run and left layout L.
+void finish_gates(sv_state *s, const int32_t *L, const SeqGate *g, const SeqGate *end) {
   for (int i = 0; i < s->n; ++i) {
-    s->L[i] = Lend[i];
-    s->Linv[Lend[i]] = i;
+    s->L[i] = L[i];
+    s->Linv[L[i]] = i;
   }
-  for (const SeqGate &g : gates) {
+  for (; g != end; ++g) {
     ++s->clock;
-    for (int j = 0; j < g.k; ++j) s->last_use[g.t[j]] = s->clock;
+    for (int j = 0; j < g->k; ++j) s->last_use[g->t[j]] = s->clock;
   }
 }
+
+// The statistics of gates that run: counted by gate when they have, whatever
+// their launches counted meanwhile; of gates that failed only what was settled.
+class Count {
+ public:
+  explicit Count(sv_state *s) : s_(s), settled_(s->stats) { std::memset(&add, 0, sizeof(add)); }
+  ~Count() { s_->stats = settled_; }
+  void settle() {  // the gates counted in add have run
+    add.launches = s_->stats.launches - settled_.launches;
+    add_stats(&settled_, add);
+    std::memset(&add, 0, sizeof(add));
+    s_->stats = settled_;
+  }
+  sv_stats add;
+
+ private:
+  sv_state *s_;
+  sv_stats settled_;
+};
 
 // One launch of a sequence (a diagonal gate's few): a gate's own sweep, a fused
 // pass, a gate chain or a program, and the operand it reads in device memory.
@@ -726,8 +746,9 @@ class Runner {
 
 // Runs a sequence of valid gates.
 int run_steps(sv_state *s, const std::vector<SeqGate> &gates) {
-  const sv_stats before = s->stats;
+  Count count(s);
   Steps steps(s, gates);
+  count.add = steps.add;
   Runner run(s);
   for (std::unique_ptr<Step> st;;) {
     int rc = steps.next(&st);
@@ -738,67 +759,68 @@ int run_steps(sv_state *s, const std::vector<SeqGate> &gates) {
   }
   const int rc = run.flush();
   if (rc) return rc;
-  steps.add.launches = s->stats.launches - before.launches;
-  s->stats = before;
-  add_stats(&s->stats, steps.add);
-  finish_sequence(s, steps.Lend, gates);
+  count.settle();
+  finish_gates(s, steps.Lend, gates.data(), gates.data() + gates.size());
   return SV_OK;
 }
 
 // Runs a list of valid gates in order (sv_apply_gates on a fusible handle):
 // narrow gates in a row share program passes (sv_prog_host.h), any other gate
-// has its own sweep.
+// has its own sweep.  The handle follows with its layout and statistics when
+// gates have run: a failed launch leaves those of the gates before it.
 int run_list(sv_state *s, const std::vector<SeqGate> &gates) {
-  sv_stats total = s->stats;
-  std::vector<pass::Item> run;
-  std::vector<prog::Step> steps;
-  auto single = [&](const pass::Item &it) {
-    const int64_t l0 = s->stats.launches;
-    const int rc = apply_physical(s, it.m, it.A, it.k);
-    total.launches += s->stats.launches - l0;
-    return rc;
+  Count count(s);
+  int32_t L[64];
+  std::memcpy(L, s->L, sizeof(L));
+  const SeqGate *settled = gates.data();
+  auto settle = [&](const SeqGate *end) {
+    count.settle();
+    finish_gates(s, L, settled, end);
+    settled = end;
   };
-  auto flush = [&]() -> int {
-    if (run.empty()) return SV_OK;
-    steps.clear();
-    prog::build(s->n, run, &steps);
-    for (const prog::Step &x : steps) {
-      if (!x.fused) {
-        for (int i : x.items) {
-          const int rc = single(run[size_t(i)]);
-          if (rc) return rc;
+  std::vector<pass::Item> run;  // narrow gates from `settled` on
+  std::vector<prog::Step> steps;
+  auto flush = [&](const SeqGate *end) -> int {
+    if (!run.empty()) {
+      steps.clear();
+      prog::build(s->n, run, &steps);
+      for (const prog::Step &x : steps) {
+        if (!x.fused) {
+          for (int i : x.items) {
+            const pass::Item &it = run[size_t(i)];
+            const int rc = apply_physical(s, it.m, it.A, it.k);
+            if (rc) return rc;
+          }
+          continue;
         }
-        continue;
+        const hipError_t e = prog::launch(x.args, s->amps, s->st);
+        if (e != hipSuccess) {
+          set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
+          return SV_ERR_DEVICE;
+        }
+        s->stats.launches += 1;
       }
-      const hipError_t e = prog::launch(x.args, s->amps, s->st);
-      if (e != hipSuccess) {
-        set_error(std::string("kernel launch failed: ") + hipGetErrorString(e));
-        return SV_ERR_DEVICE;
-      }
-      total.launches += 1;
+      run.clear();
     }
-    run.clear();
+    settle(end);
     return SV_OK;
   };
   pass::Item it;
-  int rc = SV_OK;
   for (const SeqGate &g : gates) {
-    const bool work = resolve_gate(s->n, g, s->L, &total, &it);
-    for (int j = 0; j < g.k; ++j) s->Linv[s->L[g.t[j]]] = g.t[j];
-    ++s->clock;
-    for (int j = 0; j < g.k; ++j) s->last_use[g.t[j]] = s->clock;
-    if (!work) continue;
-    if (s->n >= prog::kMinQubits && prog::takes(it)) {
+    sv_stats one;
+    std::memset(&one, 0, sizeof(one));
+    const bool work = resolve_gate(s->n, g, L, &one, &it);  // a gate with work leaves L as it is
+    if (work && s->n >= prog::kMinQubits && prog::takes(it)) {
       run.push_back(it);
-      continue;
+    } else if (work) {
+      int rc = flush(&g);
+      if (rc == SV_OK) rc = apply_physical(s, it.m, it.A, it.k);
+      if (rc) return rc;
     }
-    rc = flush();
-    if (rc == SV_OK) rc = single(it);
-    if (rc) break;
+    add_stats(&count.add, one);
+    if (run.empty()) settle(&g + 1);
   }
-  if (rc == SV_OK) rc = flush();
-  s->stats = total;
-  return rc;
+  return flush(gates.data() + gates.size());
 }
 
 }  // namespace
@@ -1597,8 +1619,8 @@ int sv_bound_run(sv_bound *b) {
     if (rc) return rc;
     const sv_stats before = b->s->stats;
     rc = bound_launch_all(b);
-    if (rc) return rc;
     b->s->stats = before;
+    if (rc) return rc;
     add_stats(&b->s->stats, b->per_run);
     bound_finish(b);
     return SV_OK;

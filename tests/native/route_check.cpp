@@ -344,11 +344,59 @@ void narrow_gates_packed_lean() {
   }
 }
 
+// A launch that fails leaves the layout and statistics of the gates before it.
+void failed_launch_in_a_list() {
+  const int n = 12;
+  const Gate h2 = dense({2}), h3 = dense({3}), h5 = dense({5}), wide = dense({1, 4, 6, 8, 9});
+  // launches: gates 1 and 2 as a program, gate 4 by itself, gates 5 and 7 as a program
+  const std::vector<Gate> gates = {swap(0, 1), h2, h3, swap(2, 7), wide, h5, swap(3, 10), h2, swap(4, 5)};
+  const size_t ran[] = {1, 4, 5};  // gates known to have run when launch i fails
+  for (long fail = 0; fail < 3; ++fail) {
+    sv_state *a = state(n), *b = state(n);
+    rt::fail_at = fail;
+    CHECK(apply_list(a, gates) == SV_ERR_DEVICE, "launch %ld did not fail", fail);
+    rt::fail_at = -1;
+    CHECK(apply_list(b, std::vector<Gate>(gates.begin(), gates.begin() + long(ran[fail]))) == SV_OK, "%s", sv_last_error());
+    CHECK(layout(a, n) == layout(b, n), "launch %ld: the layout is not that of %zu gates", fail, ran[fail]);
+    sv_stats x, y;
+    sv_get_stats(a, &x);
+    sv_get_stats(b, &y);
+    CHECK(std::memcmp(&x, &y, sizeof(x)) == 0, "launch %ld: the statistics are not those of %zu gates", fail, ran[fail]);
+    sv_free(a);
+    sv_free(b);
+  }
+}
+
+// Of a plan's run that fails nothing is recorded.
+void failed_launch_in_a_plan() {
+  for (int n : {8, 20}) {
+    std::vector<Gate> gates = mixed(n, 6, 60);
+    gates.push_back(swap(1, n - 1));
+    sv_plan *p = plan_of(n, gates);
+    sv_state *s = state(n);
+    sv_stats x, y;
+    sv_get_stats(s, &x);
+    const std::vector<int32_t> L = layout(s, n);
+    for (long fail : {0, 2, 5}) {
+      rt::fail_at = fail;
+      CHECK(sv_run_plan(s, p) == SV_ERR_DEVICE, "launch %ld did not fail", fail);
+      rt::fail_at = -1;
+      sv_get_stats(s, &y);
+      CHECK(std::memcmp(&x, &y, sizeof(x)) == 0, "n=%d launch %ld: statistics moved", n, fail);
+      CHECK(layout(s, n) == L, "n=%d launch %ld: layout moved", n, fail);
+    }
+    sv_free(s);
+    sv_plan_free(p);
+  }
+}
+
 const std::map<std::string, std::function<void()>> kChecks = {
     {"packed_once", packed_once},
     {"bound_bytes_cheap_and_enough", bound_bytes_cheap_and_enough},
     {"bound_runs_what_the_plan_runs", bound_runs_what_the_plan_runs},
     {"narrow_gates_packed_lean", narrow_gates_packed_lean},
+    {"failed_launch_in_a_list", failed_launch_in_a_list},
+    {"failed_launch_in_a_plan", failed_launch_in_a_plan},
     {"long_plan_bounded", long_plan_bounded},
     {"first_copy_early", first_copy_early},
 };
