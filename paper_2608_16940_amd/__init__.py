@@ -35,20 +35,28 @@ def _stream_ptr(stream):
 
 
 _LIST_CHUNK = 1024  # gates per call: bounds the copy of their matrices (64 MiB at six qubits)
+_LIST_QUBITS = 6    # widest gate of a list call
+
+
+def _listable(gate):
+    try:
+        return isinstance(gate.targets, (tuple, list, np.ndarray)) and len(gate.targets) <= _LIST_QUBITS
+    except Exception:
+        return False
 
 
 def _gate_list(gates):
-    """Arguments of sv_apply_gates, or None for a list that is not one complex matrix of
-    2^k x 2^k and k <= 6 integers per gate (applied one by one, so that what precedes a bad gate acts)."""
+    """Arguments of sv_apply_gates, or None for a list that is not one complex matrix of 2^k x 2^k
+    and k integers per gate (applied one by one, so that what precedes a bad gate acts)."""
     try:
         targets = [g.targets for g in gates]
         ks = [len(t) for t in targets]
         matrices = [np.ascontiguousarray(g.matrix, np.complex128) for g in gates]
-        if max(ks) > 6 or [m.size for m in matrices] != [1 << (2 * k) for k in ks]:
+        if [m.size for m in matrices] != [1 << (2 * k) for k in ks]:
             return None
         ks = array.array("i", ks)
         flat = array.array("i", itertools.chain.from_iterable(targets))
-    except (TypeError, ValueError, OverflowError, AttributeError):
+    except Exception:  # whatever a gate's attributes raise is raised when its turn comes
         return None
     # the library copies what it needs before it returns
     return len(gates), bytes(ks), bytes(flat), b"".join(matrices)
@@ -108,13 +116,14 @@ class StateVector:
                 self.apply(g.matrix, g.targets)
             return
         for i in range(0, len(gates), _LIST_CHUNK):
-            part = gates[i:i + _LIST_CHUNK]
-            call = _gate_list(part)
-            if call is not None:
-                check(lib().sv_apply_gates(self._h, *call))
-                continue
-            for g in part:
-                self.apply(g.matrix, g.targets)
+            for listable, part in itertools.groupby(gates[i:i + _LIST_CHUNK], _listable):
+                part = list(part)
+                call = _gate_list(part) if listable else None
+                if call is not None:
+                    check(lib().sv_apply_gates(self._h, *call))
+                    continue
+                for g in part:
+                    self.apply(g.matrix, g.targets)
 
     def permute_layout(self, layout):
         L = np.ascontiguousarray(np.asarray(layout, dtype=np.int32))
