@@ -35,22 +35,23 @@ def _stream_ptr(stream):
 
 
 _LIST_CHUNK = 1024  # gates per call: bounds the copy of their matrices (64 MiB at six qubits)
-_LIST_QUBITS = 6    # widest gate of a list call
-
-
-def _listable(gate):
-    try:
-        return isinstance(gate.targets, (tuple, list, np.ndarray)) and len(gate.targets) <= _LIST_QUBITS
-    except Exception:
-        return False
 
 
 def _gate_list(gates):
-    """Arguments of sv_apply_gates, or None for a list that is not one complex matrix of 2^k x 2^k
-    and k integers per gate (applied one by one, so that what precedes a bad gate acts)."""
+    """Arguments of sv_apply_gates, or None for a list that is not one complex matrix of
+    2^k x 2^k and k <= 6 integers per gate (applied one by one, so that what precedes a bad gate acts)."""
     try:
         targets = [g.targets for g in gates]
-        ks = [len(t) for t in targets]
+        try:
+            ks = list(map(tuple.__len__, targets))
+        except TypeError:
+            if not all(isinstance(t, (tuple, list, np.ndarray)) for t in targets):
+                return None  # sets, bytes, single numbers: apply's to take or refuse
+            ks = [len(t) for t in targets]
+        # six-qubit gates alone gain nothing from a list and pay for the copy (64 KiB each; six of them on
+        # 12 qubits 182 us one by one, 193 as a list)
+        if max(ks) > 5 and (max(ks) > 6 or 2 * ks.count(6) > len(ks)):
+            return None
         matrices = [np.ascontiguousarray(g.matrix, np.complex128) for g in gates]
         if [m.size for m in matrices] != [1 << (2 * k) for k in ks]:
             return None
@@ -116,14 +117,13 @@ class StateVector:
                 self.apply(g.matrix, g.targets)
             return
         for i in range(0, len(gates), _LIST_CHUNK):
-            for listable, part in itertools.groupby(gates[i:i + _LIST_CHUNK], _listable):
-                part = list(part)
-                call = _gate_list(part) if listable else None
-                if call is not None:
-                    check(lib().sv_apply_gates(self._h, *call))
-                    continue
-                for g in part:
-                    self.apply(g.matrix, g.targets)
+            part = gates[i:i + _LIST_CHUNK]
+            call = _gate_list(part)
+            if call is not None:
+                check(lib().sv_apply_gates(self._h, *call))
+                continue
+            for g in part:
+                self.apply(g.matrix, g.targets)
 
     def permute_layout(self, layout):
         L = np.ascontiguousarray(np.asarray(layout, dtype=np.int32))

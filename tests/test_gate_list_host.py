@@ -50,6 +50,18 @@ def test_what_precedes_a_gate_that_raises_is_applied(sv):
         assert sv.calls == [("apply", 1), ("apply", 2)]
 
 
+def test_lists_of_wide_gates_go_one_by_one(sv):
+    six = Gate(tuple(range(6)))
+    sv.apply_gates([six, six, Gate((0,))])
+    assert sv.calls == [("apply", 6), ("apply", 6), ("apply", 1)]
+    sv.calls.clear()
+    sv.apply_gates([Gate((0,)), six, Gate((1, 0)), Gate(tuple(range(5)))])
+    assert sv.calls == [("list", [1, 6, 2, 5])]
+    sv.calls.clear()
+    sv.apply_gates([Gate((0,)), Gate(tuple(range(7)))])
+    assert sv.calls == [("apply", 1), ("apply", 7)]
+
+
 def test_targets_that_apply_refuses_stay_refused(sv):
     for bad in ({0}, {0: 1}, "a", b"a"):
         g = Gate((0,))
@@ -57,7 +69,7 @@ def test_targets_that_apply_refuses_stay_refused(sv):
         sv.calls.clear()
         with pytest.raises(Exception):
             sv.apply_gates([Gate((1,)), g])
-        assert sv.calls == [("list", [1])]
+        assert sv.calls == [("apply", 1)]
 
 
 def test_arrays_and_lists_as_targets(sv):
