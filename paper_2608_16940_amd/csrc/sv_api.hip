@@ -245,15 +245,16 @@ bool is_diagonal(const double *m, int k) {
 
 // Choose the kernel for a gate on physical targets A (the selector of the
 // lowering step; Section IV-E) and say how many bytes its operand takes in
-// device memory (0: by value).
-int select(const sv_state *s, const double *matrix, const int32_t *A, int k, int *variant, size_t *bytes) {
+// device memory (0: by value).  diag: is_diagonal(matrix, k), which reads all of
+// a diagonal matrix and so is asked once per gate (seven qubits: 27 us, 53 when
+// asked twice).
+int select(const sv_state *s, bool diag, const int32_t *A, int k, int *variant, size_t *bytes) {
   const int n = s->n;
   int v = s->variant;
   const bool shuffle_ok = (k == 1 && A[0] <= 6);
   const bool mfma_ok = (k >= 4 && k <= 7 && n >= k + mfma_tile_M(k));
   const bool valu_ok = (k <= 4);
   const size_t D = size_t(1) << k;
-  const bool diag = is_diagonal(matrix, k);
   if (v == SV_VARIANT_AUTO) {
     if (diag)
       v = SV_VARIANT_DIAG;
@@ -304,11 +305,11 @@ int select(const sv_state *s, const double *matrix, const int32_t *A, int k, int
 }
 
 // Select the kernel for a gate and prepare its operands.
-int lower(const sv_state *s, const double *matrix, const int32_t *A, int k, bool allow_relabel, Lowered *L) {
+int lower(const sv_state *s, const double *matrix, bool diag, const int32_t *A, int k, bool allow_relabel, Lowered *L) {
   const int n = s->n, D = 1 << k;
   int v = 0;
   size_t bytes = 0;
-  const int rc = select(s, matrix, A, k, &v, &bytes);
+  const int rc = select(s, diag, A, k, &v, &bytes);
   if (rc) return rc;
   L->op.resize(bytes);
   L->variant = v;
@@ -417,9 +418,9 @@ int launch_lowered(sv_state *s, const Lowered &L, const void *op_dev) {
   return SV_OK;
 }
 
-int apply_physical(sv_state *s, const double *matrix, const int32_t *A, int k) {
+int apply_physical(sv_state *s, const double *matrix, bool diag, const int32_t *A, int k) {
   Lowered L;
-  int rc = lower(s, matrix, A, k, true, &L);
+  int rc = lower(s, matrix, diag, A, k, true, &L);
   if (rc) return rc;
   if (L.op.empty()) return launch_lowered(s, L, nullptr);
   void *dev = nullptr;
@@ -648,7 +649,7 @@ class Steps {
     singles_.pop_back();
     std::unique_ptr<Step> st(new Step);
     Lowered &L = st->what.emplace<Lowered>();
-    const int rc = lower(s_, it.m, it.A, it.k, false, &L);
+    const int rc = lower(s_, it.m, it.diag, it.A, it.k, false, &L);
     if (rc) return rc;
     st->op = std::move(L.op);
     *out = std::move(st);
@@ -788,7 +789,7 @@ int run_list(sv_state *s, const std::vector<SeqGate> &gates) {
         if (!x.fused) {
           for (int i : x.items) {
             const pass::Item &it = run[size_t(i)];
-            const int rc = apply_physical(s, it.m, it.A, it.k);
+            const int rc = apply_physical(s, it.m, it.diag, it.A, it.k);
             if (rc) return rc;
           }
           continue;
@@ -814,7 +815,7 @@ int run_list(sv_state *s, const std::vector<SeqGate> &gates) {
       run.push_back(it);
     } else if (work) {
       int rc = flush(&g);
-      if (rc == SV_OK) rc = apply_physical(s, it.m, it.A, it.k);
+      if (rc == SV_OK) rc = apply_physical(s, it.m, it.diag, it.A, it.k);
       if (rc) return rc;
     }
     add_stats(&count.add, one);
@@ -961,7 +962,7 @@ int sv_apply_fused(sv_state *s, const double *matrix, const int32_t *targets, in
       for (int j = 0; j < k; ++j) s->last_use[targets[j]] = s->clock;
       return SV_OK;
     }
-    const int rc = apply_physical(s, matrix, A, k);
+    const int rc = apply_physical(s, matrix, is_diagonal(matrix, k), A, k);
     if (rc == SV_OK) {
       ++s->clock;
       for (int j = 0; j < k; ++j) s->last_use[targets[j]] = s->clock;
@@ -1396,7 +1397,7 @@ int bound_bytes(const sv_state *s, const sv_plan *p, size_t *bytes) {
       continue;
     }
     size_t own = 0;
-    rc = select(s, g.m, A, g.k, &v, &own);
+    rc = select(s, is_diagonal(g.m, g.k), A, g.k, &v, &own);
     if (rc) return rc;
     *bytes += align256(std::max(own, fuse ? pass::share_bytes(s->n, g.k, v == SV_VARIANT_DIAG, s->prec) : 0));
   }
@@ -1449,7 +1450,7 @@ int lower_plan(sv_state *s, const sv_plan *p, sv_bound *b, size_t *bytes) {
       }
       std::unique_ptr<Step> st(new Step);
       Lowered &L = st->what.emplace<Lowered>();
-      const int rc = lower(s, g.m, A, g.k, false, &L);
+      const int rc = lower(s, g.m, is_diagonal(g.m, g.k), A, g.k, false, &L);
       if (rc) return rc;
       st->op = std::move(L.op);
       b->per_run.gate_sweeps += 1;
