@@ -140,6 +140,7 @@ std::vector<BGate> group_run(const std::vector<BGate> &g, size_t a, size_t b, in
 // whose value on each basis vector e_b is mask[b].
 std::vector<BGate> merge_cnots(const std::vector<BGate> &g, size_t a, size_t b) {
   std::vector<BGate> out;
+  out.reserve(b - a);
   size_t i = a;
   while (i < b) {
     size_t j = i;
@@ -352,7 +353,7 @@ int pack_batch(int count, const sv_batch_circuit *circs, size_t states_bytes, co
       it.n = n;
       it.P = P;
       int ng = 0;
-      it.flags = kItemFinite;
+      it.flags = n > kSliceBits ? kItemFinite : 0;
       for (int c = 0; c < P; ++c) {
         const int id = ids[pos + size_t(c)];
         it.circ[c] = id;
@@ -362,10 +363,12 @@ int pack_batch(int count, const sv_batch_circuit *circs, size_t states_bytes, co
         it.gate_off[c] = gate_off[size_t(id)];
         it.state_off[c] = state_offsets[id] / 8;
         for (const BGate &b : fused[size_t(id)]) {
-          if (b.kind == SV_BATCH_GATE_LINEAR && n <= kSliceBits) it.flags |= kItemLinear;
-          if (b.kind == SV_BATCH_GATE_1Q)
+          if (n <= kSliceBits) {
+            if (b.kind == SV_BATCH_GATE_LINEAR) it.flags |= kItemLinear;
+          } else if (b.kind == SV_BATCH_GATE_1Q) {
             for (float v : b.m)
               if (!std::isfinite(v)) it.flags &= ~kItemFinite;
+          }
         }
       }
       it.ngates = ng;

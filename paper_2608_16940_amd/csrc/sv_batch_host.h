@@ -29,7 +29,7 @@ struct BGate {
   float m[8];  // 2x2 complex64 row-major interleaved
 };
 
-constexpr int kItemFinite = 1;  // no matrix holds an infinity or a NaN
+constexpr int kItemFinite = 1;  // a circuit in passes, no matrix of which holds an infinity or a NaN
 constexpr int kItemLinear = 2;  // a circuit of the pack has a linear record (states in LDS)
 
 struct BItem {
