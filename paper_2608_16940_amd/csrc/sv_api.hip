@@ -1028,7 +1028,7 @@ int sv_permute_layout(sv_state *s, const int32_t *new_layout) {
     // that takes fewer.
     std::vector<PermPass> passes = permutation_tiles(s->L, new_layout, n, kPermTileBits);
     int S = kPermTileBits;
-    if (n >= kPermWideBits) {
+    if (n >= kPermWideBits && passes.size() > 1) {
       std::vector<PermPass> wide = permutation_tiles(s->L, new_layout, n, kPermWideBits);
       if (wide.size() < passes.size()) {
         passes.swap(wide);
