@@ -166,7 +166,15 @@ int sv_plan_block_swap(const sv_plan *p, int i, int *is_swap, int32_t *dest);
  * several to a pass over the state (FP32: dense blocks of up to 6 qubits and
  * diagonal ones; BF16x3: diagonal blocks of entries 1, -1, i, -i), blocks on
  * different qubits in either order; statistics count blocks as before, and
- * launches the kernels that ran.  After SV_ERR_DEVICE the amplitudes are
+ * launches the kernels that ran.  FP32 passes of dense blocks hold an amplitude
+ * in three bf16 pieces: magnitudes from 2^-104 up to the largest bf16, just
+ * under 2^128, keep FP32's accuracy (2^-114: 2e-6, 2^-122: 4e-4).  An infinity
+ * or a NaN in the state reaches all 32 or 64 amplitudes it is multiplied with,
+ * also where the block itself acts on fewer qubits, and one in a matrix makes
+ * the block's results undefined; blocks that run by themselves touch only the
+ * 2^k amplitudes of a group.  Sequences of dense blocks of at most four qubits
+ * with no diagonal among them run block by block (the swaps of sv_plan_swaps
+ * are priced by that).  After SV_ERR_DEVICE the amplitudes are
  * undefined: some blocks between two layout swaps have run, not always the
  * first ones, and layout and statistics do not count them; sv_reset makes the
  * handle usable again. */

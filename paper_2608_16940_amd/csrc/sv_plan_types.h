@@ -1,5 +1,5 @@
 // A plan's fused blocks, shared by the planners (sv_plan.cpp) and the code
-// that runs them (sv_run.hip).  Plain C++, no HIP.
+// that runs them (sv_api.hip).  Plain C++, no HIP.
 #pragma once
 
 #include <cstdint>
