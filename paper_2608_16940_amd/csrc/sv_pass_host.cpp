@@ -508,7 +508,12 @@ struct Cutter::Draws {
   // sweeps: the layout swaps of sv_plan_swaps are priced by those, and a
   // sequence that gained the same from passes would make them a loss (20 + 20
   // alternating four-bit gates at N=30: 52 ms in passes with or without the
-  // swap's 3 ms permutation; 117 and 98 ms in single sweeps).
+  // swap's 3 ms permutation; 117 and 98 ms in single sweeps).  The price is
+  // paid by sequences that no swap helps: 40 four-bit gates, replayed, take 126
+  // us in sweeps and 86 in passes at n=12, 269 and 123 at 20, 1023 and 502 at
+  // 23.  Of narrow gates on small states and of few gates sweeps are the better
+  // choice (launched, 40 two-bit gates at n=14: 103 and 124 us; four four-bit
+  // ones: 26 and 31).
   bool plain = true;
   std::vector<int> alone;  // drafted items that run by their own sweeps, the next one last
 
