@@ -226,7 +226,7 @@ struct Lowered {
   int k = 0;
   int32_t A[8] = {0};
   DiagCover cover;             // diagonal: the subcubes its sweeps visit
-  float2 m[256];               // by value: VALU matrix, shuffle 2x2, diagonal table with k <= 4
+  std::vector<float2> m;       // by value: VALU matrix, shuffle 2x2, diagonal table with k <= 4
   bool by_value = false;
   std::vector<char> op;        // device operand bytes (empty when by value)
   TilePlan tp;                 // MFMA tile geometry
@@ -319,7 +319,9 @@ int lower(const sv_state *s, const double *matrix, bool diag, const int32_t *A, 
   L->opsrc = s->opsrc;
   switch (v) {
     case SV_VARIANT_DIAG: {
-      std::vector<float2> d(static_cast<size_t>(D));
+      L->by_value = bytes == 0;
+      if (L->by_value) L->m.resize(size_t(D));
+      float2 *d = L->by_value ? L->m.data() : reinterpret_cast<float2 *>(L->op.data());
       for (int r = 0; r < D; ++r)
         d[r] = make_float2(float(matrix[2 * (r * D + r)]), float(matrix[2 * (r * D + r) + 1]));
       std::vector<double> dd(2 * size_t(D));
@@ -328,17 +330,13 @@ int lower(const sv_state *s, const double *matrix, bool diag, const int32_t *A, 
         dd[2 * size_t(r) + 1] = matrix[2 * (r * D + r) + 1];
       }
       L->cover = diag_cover(k, dd.data(), A);
-      L->by_value = bytes == 0;
-      if (L->by_value)
-        for (int r = 0; r < D; ++r) L->m[r] = d[r];
-      else
-        std::memcpy(L->op.data(), d.data(), bytes);
       return SV_OK;
     }
     case SV_VARIANT_SHUFFLE:
     case SV_VARIANT_VALU:
       L->by_value = true;
-      for (int i = 0; i < D * D; ++i) L->m[i] = make_float2(float(matrix[2 * i]), float(matrix[2 * i + 1]));
+      L->m.resize(size_t(D) * D);
+      for (int i = 0; i < D * D; ++i) L->m[size_t(i)] = make_float2(float(matrix[2 * i]), float(matrix[2 * i + 1]));
       return SV_OK;
     case SV_VARIANT_MFMA: {
       if (s->lazy && allow_relabel) L->relabel = plan_relabel(s, A, k, mfma_tile_M(k));
@@ -394,13 +392,13 @@ int launch_lowered(sv_state *s, const Lowered &L, const void *op_dev) {
             fv |= ((L.cover.val[i] >> j) & 1) << nf;
             ++nf;
           }
-        e = L.by_value ? launch_diag(s->amps, n, L.k, L.A, nullptr, L.m, nf, fp, fv, s->st)
+        e = L.by_value ? launch_diag(s->amps, n, L.k, L.A, nullptr, L.m.data(), nf, fp, fv, s->st)
                        : launch_diag(s->amps, n, L.k, L.A, static_cast<const float2 *>(op_dev), nullptr, nf, fp, fv,
                                      s->st);
       }
       break;
-    case SV_VARIANT_SHUFFLE: e = launch_1q_shuffle(s->amps, n, L.A[0], L.m, s->st); break;
-    case SV_VARIANT_VALU: e = launch_dense_valu(s->amps, n, L.k, L.A, L.m, s->st); break;
+    case SV_VARIANT_SHUFFLE: e = launch_1q_shuffle(s->amps, n, L.A[0], L.m.data(), s->st); break;
+    case SV_VARIANT_VALU: e = launch_dense_valu(s->amps, n, L.k, L.A, L.m.data(), s->st); break;
     case SV_VARIANT_MFMA: e = launch_tile_mfma(L.tp, L.prec, L.opsrc, s->amps, op_dev, s->st); break;
     case SV_VARIANT_GENERIC:
       e = launch_dense_generic(s->amps, n, L.k, L.A, static_cast<const float2 *>(op_dev), s->st);
