@@ -11,6 +11,7 @@
 #include <random>
 
 #include "sv.h"
+#include "sv_batch.h"
 #include "sv_density.h"
 #include "sv_plan.h"
 
@@ -390,6 +391,33 @@ void failed_launch_in_a_plan() {
   }
 }
 
+// The records of a small batch go to the device by one copy, circuits in passes included.
+void small_batch_one_copy() {
+  for (int n : {6, 15, 18}) {
+    std::vector<int32_t> kinds, qubits;
+    std::vector<double> mats;
+    for (int q = 0; q < n; ++q) {
+      kinds.push_back(SV_BATCH_GATE_1Q);
+      qubits.insert(qubits.end(), {q, -1});
+      for (int e = 0; e < 8; ++e) mats.push_back(uniform());
+    }
+    sv_batch_circuit c{};
+    c.n_qubits = n;
+    c.n_gates = int(kinds.size());
+    c.kinds = kinds.data();
+    c.qubits = qubits.data();
+    c.mats = mats.data();
+    const int64_t off = 0;
+    sv_batch_prepared *p = nullptr;
+    rt::start();
+    CHECK(sv_batch_prepare(1, &c, size_t(8) << n, &off, nullptr, kWork, sv_batch_workspace_bytes(1, &c), nullptr, &p) == SV_OK,
+          "%s", sv_last_error());
+    rt::stop();
+    CHECK(rt::events().size() == 1, "n=%d: %zu copies", n, rt::events().size());
+    sv_batch_prepared_free(p);
+  }
+}
+
 const std::map<std::string, std::function<void()>> kChecks = {
     {"packed_once", packed_once},
     {"bound_bytes_cheap_and_enough", bound_bytes_cheap_and_enough},
@@ -397,6 +425,7 @@ const std::map<std::string, std::function<void()>> kChecks = {
     {"narrow_gates_packed_lean", narrow_gates_packed_lean},
     {"failed_launch_in_a_list", failed_launch_in_a_list},
     {"failed_launch_in_a_plan", failed_launch_in_a_plan},
+    {"small_batch_one_copy", small_batch_one_copy},
     {"long_plan_bounded", long_plan_bounded},
     {"first_copy_early", first_copy_early},
 };
