@@ -44,7 +44,7 @@ typedef struct sv_batch_circuit {
  * state is to stay in LDS; larger n must use 1).  Index 0 is unused. */
 #define SV_BATCH_CONFIG_LEN (SV_BATCH_MAX_QUBITS + 1)
 
-/* Device workspace bytes for a batch (gate records, pack table, queue). */
+/* Device workspace bytes for a batch (gate records, tables of packs and passes, shares of <Z_0>). */
 size_t sv_batch_workspace_bytes(int count, const sv_batch_circuit *circs);
 
 /*
