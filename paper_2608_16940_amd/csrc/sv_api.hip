@@ -426,9 +426,8 @@ int apply_physical(sv_state *s, const double *matrix, bool diag, const int32_t *
   rc = stage(s, {{L.op.data(), L.op.size()}}, &dev, &slot);
   if (rc) return rc;
   rc = launch_lowered(s, L, dev);
-  if (rc) return rc;
-  rc = release_slot(s, slot);
-  if (rc) return rc;
+  const int freed = release_slot(s, slot);
+  if (rc || freed) return rc ? rc : freed;
   for (auto &pr : L.relabel) swap_physical(s, pr.first, pr.second);
   s->stats.relabels += int64_t(L.relabel.size());
   return SV_OK;
@@ -725,14 +724,19 @@ class Runner {
       if (rc) return rc;
     }
     size_t at = 0;
+    int rc = SV_OK;
     for (const auto &st : held_) {
-      const int rc = launch_step(s_, *st, static_cast<const char *>(dev) + at);
-      if (rc) return rc;
+      rc = launch_step(s_, *st, static_cast<const char *>(dev) + at);
+      if (rc) break;
       at += align256(st->op.size());
     }
     held_.clear();
     bytes_ = 0;
-    return slot >= 0 ? release_slot(s_, slot) : SV_OK;
+    if (slot >= 0) {  // also after a failed launch: the copy and the launches before it still read the slot
+      const int freed = release_slot(s_, slot);
+      if (rc == SV_OK) rc = freed;
+    }
+    return rc;
   }
 
  private:

@@ -32,11 +32,13 @@ inline std::map<const void *, std::string> &kernels() {
   return k;
 }
 inline long fail_at = -1;  // launches until one fails
+inline size_t recorded = 0;  // events recorded since start()
 inline size_t allocated = 0, live = 0, peak = 0;  // host bytes since start()
 inline bool counting = false;
 
 inline void start() {
   events().clear();
+  recorded = 0;
   allocated = live = peak = 0;
   counting = true;
 }
@@ -154,7 +156,10 @@ hipError_t hipEventCreate(hipEvent_t *e) {
 }
 hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) {
+  ++rt::recorded;
+  return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) {
   *ms = 0.f;

@@ -368,6 +368,31 @@ void failed_launch_in_a_list() {
   }
 }
 
+// A staging slot whose copy was issued is released also when a launch fails:
+// its next user waits for the copy.
+void failed_launch_releases_its_slot() {
+  const int n = 20;
+  std::vector<Gate> gates;
+  for (int i = 0; i < 30; ++i) gates.push_back(dense(targets(n, 6)));
+  sv_plan *p = plan_of(n, gates);
+  sv_state *s = state(n);
+  for (long fail : {0, 1, 3}) {
+    for (int one = 0; one < 2; ++one) {
+      rt::start();
+      rt::fail_at = one ? 0 : fail;
+      const int rc = one ? sv_apply_fused(s, gates[0].m.data(), gates[0].t.data(), 6) : sv_run_plan(s, p);
+      CHECK(rc == SV_ERR_DEVICE, "launch %ld did not fail", fail);
+      rt::fail_at = -1;
+      rt::stop();
+      size_t copies = 0;
+      for (const rt::Event &e : rt::events()) copies += e.kernel.empty();
+      CHECK(copies > 0 && copies == rt::recorded, "launch %ld: %zu copies, %zu slots released", fail, copies, rt::recorded);
+    }
+  }
+  sv_free(s);
+  sv_plan_free(p);
+}
+
 // Of a plan's run that fails nothing is recorded.
 void failed_launch_in_a_plan() {
   for (int n : {8, 20}) {
@@ -426,6 +451,7 @@ const std::map<std::string, std::function<void()>> kChecks = {
     {"failed_launch_in_a_list", failed_launch_in_a_list},
     {"failed_launch_in_a_plan", failed_launch_in_a_plan},
     {"small_batch_one_copy", small_batch_one_copy},
+    {"failed_launch_releases_its_slot", failed_launch_releases_its_slot},
     {"long_plan_bounded", long_plan_bounded},
     {"first_copy_early", first_copy_early},
 };

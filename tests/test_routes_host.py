@@ -36,7 +36,8 @@ def exe():
 @pytest.mark.parametrize("check", ["packed_once", "first_copy_early", "long_plan_bounded",
                                    "bound_bytes_cheap_and_enough", "bound_runs_what_the_plan_runs",
                                    "narrow_gates_packed_lean", "small_batch_one_copy",
-                                   "failed_launch_in_a_list", "failed_launch_in_a_plan"])
+                                   "failed_launch_in_a_list", "failed_launch_in_a_plan",
+                                   "failed_launch_releases_its_slot"])
 def test_route(exe, check):
     r = subprocess.run([exe, check], capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, (r.stdout[-4000:], r.stderr[-2000:])
